@@ -263,8 +263,7 @@ int verify_tail_run(acespec_ctx *ctx, const acespec_model_desc &d, const TailWor
                                          R, D, d.rms_eps, stream)));
     h_in = (const A *)ws.a;
   } else if (sizeof(T) == 2) {  // bf16 hidden states: widen to fp16 for the f16 MFMA path
-    RUN(K_RMSNORM, launch_cast_bf16_f16((const bf16 *)hidden, (f16 *)ws.a, (size_t)R * D,
-                                        stream));
+    RUN(K_RMSNORM, launch_cast_bf16_f16((const bf16 *)hidden, (f16 *)ws.a, R, D, stream));
     h_in = (const A *)ws.a;
   }
   int ntile = 0;

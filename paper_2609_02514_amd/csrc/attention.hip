@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NW * 64) void tree_attn_mfma_kernel(
   const __amdgpu_buffer_rsrc_t kr = make_rsrc(kb, (uint32_t)((size_t)capacity * HD * 2));
   const __amdgpu_buffer_rsrc_t vr = make_rsrc(vb, (uint32_t)((size_t)capacity * HD * 2));
   const size_t row0 = (size_t)b * n1;
-  const int q_stride = H * HD;
+  const int q_stride = H * HD, rows_all = gridDim.z * n1;
   const float sscale = LOG2E / sqrtf((float)HD);   // scores -> base-2 exponent
   const float lazy = LAZY_LOG2 / sscale;           // reference threshold in score units
 
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(NW * 64) void tree_attn_mfma_kernel(
             f16x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (f16)(acc[e] * inv);
-            *(f16x4 *)(out + (row0 + r) * (size_t)q_stride + h * HD + nb * 16 + lg * 4) = v;
+            *(f16x4 *)(out + act_off((int)row0 + r, h * HD + nb * 16 + lg * 4, rows_all, q_stride)) = v;
           } else {
             const size_t item = ((size_t)b * Hkv + g) * nsplit + split;
             *(f32x4 *)(part_o + (item * QR + qi) * HD + nb * 16 + lg * 4) = acc;
@@ -475,13 +475,12 @@ __global__ __launch_bounds__(NW * 64) void tree_attn_mfma_kernel(
     const int r = qi / G, h = g * G + (qi - r * G);
     if (nsplit == 1) {
       const float inv = l > 0.f ? 1.0f / l : 0.f;
-      f16 *op = out + (row0 + r) * (size_t)q_stride + h * HD + lg * 4;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         f16x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = (f16)(o[t][nb][e] * inv);
-        *(f16x4 *)(op + nb * 16) = v;
+        *(f16x4 *)(out + act_off((int)row0 + r, h * HD + nb * 16 + lg * 4, rows_all, q_stride)) = v;
       }
     } else {
       const size_t item = ((size_t)b * Hkv + g) * nsplit + split;
@@ -575,7 +574,7 @@ __global__ __launch_bounds__(512) void tree_attn_t32_kernel(
   const __amdgpu_buffer_rsrc_t kr = make_rsrc(kb, (uint32_t)((size_t)capacity * HD * 2));
   const __amdgpu_buffer_rsrc_t vr = make_rsrc(vb, (uint32_t)((size_t)capacity * HD * 2));
   const size_t row0 = (size_t)b * n1;
-  const int q_stride = H * HD;
+  const int q_stride = H * HD, rows_all = gridDim.z * n1;
   const float sscale = LOG2E / sqrtf((float)HD);
   const float lazy = LAZY_LOG2 / sscale;
 
@@ -836,7 +835,7 @@ __global__ __launch_bounds__(512) void tree_attn_t32_kernel(
             f16x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (f16)(acc[e] * inv);
-            *(f16x4 *)(out + (row0 + r) * (size_t)q_stride + h * HD + nb * 16 + lg * 4) = v;
+            *(f16x4 *)(out + act_off((int)row0 + r, h * HD + nb * 16 + lg * 4, rows_all, q_stride)) = v;
           } else {
             *(f32x4 *)(part_o + (item * QR + qi) * HD + nb * 16 + lg * 4) = acc;
           }
@@ -857,7 +856,6 @@ __global__ __launch_bounds__(512) void tree_attn_t32_kernel(
       const int r = qi / G, h = g * G + (qi - r * G);
       if (nsplit == 1) {
         const float inv = l > 0.f ? 1.0f / l : 0.f;
-        f16 *op = out + (row0 + r) * (size_t)q_stride + h * HD + hh * 4;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -865,7 +863,8 @@ __global__ __launch_bounds__(512) void tree_attn_t32_kernel(
             f16x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (f16)(o[db][j * 4 + e] * inv);
-            *(f16x4 *)(op + db * 32 + j * 8) = v;
+            *(f16x4 *)(out + act_off((int)row0 + r, h * HD + db * 32 + j * 8 + hh * 4, rows_all,
+                                     q_stride)) = v;
           }
       } else {
         const size_t item = ((size_t)b * Hkv + g) * nsplit + split;
@@ -888,10 +887,9 @@ __global__ __launch_bounds__(512) void tree_attn_t32_kernel(
 // Merge of the split partials.  grid: (ceil(QR * HD / 4 / 256), kv heads, sessions); one
 // thread per 4 head dims of one query row.  part_ml holds (max in base-2 exponent units,
 // sum) per (item, query row).
-template <typename T>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ part_o,
                                                            const float *__restrict__ part_ml,
-                                                           T *__restrict__ out, int n1, int H,
+                                                           f16 *__restrict__ out, int n1, int H,
                                                            int Hkv, int HD, int nsplit) {
   const int g = blockIdx.y, b = blockIdx.z;
   const int G = H / Hkv, QR = G * n1, hd4 = HD >> 2;
@@ -916,11 +914,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
   }
   const float inv = den > 0.f ? 1.f / den : 0.f;
   const int r = qi / G, h = g * G + (qi - r * G);
-  T *o = out + ((size_t)b * n1 + r) * (H * HD) + h * HD + d;
-  o[0] = from_f32<T>(num.x * inv);
-  o[1] = from_f32<T>(num.y * inv);
-  o[2] = from_f32<T>(num.z * inv);
-  o[3] = from_f32<T>(num.w * inv);
+  *(f16x4 *)(out + act_off(b * n1 + r, h * HD + d, gridDim.z * n1, H * HD)) =
+      f16x4{(f16)(num.x * inv), (f16)(num.y * inv), (f16)(num.z * inv), (f16)(num.w * inv)};
 }
 
 // fp32 path: one wave per (tree row, query head); lane i owns dims i and i + 64.
@@ -1017,7 +1012,7 @@ hipError_t launch_attention<bf16>(const f16 *q, const bf16 *ck, const bf16 *cv,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nsplit == 1) return e;
   const int cblocks = (QR * (hd / 4) + 255) / 256;
-  hipLaunchKernelGGL(attn_combine_kernel<f16>, dim3(cblocks, Hkv, B), dim3(256), 0, s, part_o,
+  hipLaunchKernelGGL(attn_combine_kernel, dim3(cblocks, Hkv, B), dim3(256), 0, s, part_o,
                      part_ml, out, n1, H, Hkv, hd, nsplit);
   return hipGetLastError();
 }

@@ -10,6 +10,7 @@ typedef _Float16 f16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Storage of a bf16 model: weights and KV cache in bf16; activations handed from one
 // kernel to the next in fp16 (same MFMA rate on gfx950, 3 more mantissa bits: the
@@ -109,12 +110,19 @@ AS_DEVICE void buf_dma16(__amdgpu_buffer_rsrc_t rsrc, lds_ptr_t l, uint32_t voff
 // without (they do not allocate in L2 or the MALL).  Unlike the global-address form of the
 // LDS DMA, the compiler counts this one on vmcnt alone, so its waits for LDS reads issued
 // after it stay exact instead of waiting for every outstanding LDS access.
-AS_DEVICE void buf_dma16_stream(__amdgpu_buffer_rsrc_t rsrc, lds_ptr_t l, uint32_t voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, l, 16, voff, 0, 0, 2 /* nt */);
+AS_DEVICE void buf_dma16_stream(__amdgpu_buffer_rsrc_t rsrc, lds_ptr_t l, uint32_t voff,
+                                int soff = 0) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, l, 16, voff, soff, 0, 2 /* nt */);
 }
 AS_DEVICE __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
                                            0x00020000);
+}
+
+// A 16-byte buffer load at rsrc + voff + soff; past the resource's size it returns zeros
+// without a fetch.  NT: nontemporal cache policy.
+template <bool NT> AS_DEVICE u32x4 buf_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, int soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, NT ? 2 : 0);
 }
 
 // Waits until at most VM vector-memory loads of this wave are outstanding (leaves the
@@ -136,6 +144,28 @@ AS_DEVICE void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Where element (row, col) of a bf16 model's activation matrix [M, K] (K % 32 == 0) lives:
+// 16-row blocks, each holding its K / 8 eight-column pieces in turn, a piece's rows (16, or
+// the M % 16 rows of a last partial block) side by side.  One 16-row, 32-column operand of
+// v_mfma_f32_16x16x32_f16 is then one contiguous 1 KB run in lane order (lane l: row l % 16,
+// columns (l / 16) * 8 .. +8), so the GEMMs fetch it with a single fully contiguous LDS DMA
+// and read it back without bank conflicts or swizzles.  Row-major activations reached the
+// LDS as sixteen 64-byte row segments a KB, at half the address unit's rate.  The matrix
+// takes M * K elements as before.
+AS_DEVICE size_t act_off(int row, int col, int M, int K) {
+  const int r0 = row & ~15, rl = M - r0 < 16 ? M - r0 : 16;
+  return (size_t)r0 * K + (size_t)((col >> 3) * rl + (row & 15)) * 8 + (col & 7);
+}
+
+// Maps a workgroup id onto a tile (or row) id so that consecutive ids share an XCD
+// (workgroups are dealt round-robin over the 8 XCDs).
+AS_DEVICE int xcd_tile(int bid, int total) {
+  const int x = bid & 7, local = bid >> 3;
+  const int q = total >> 3, rem = total & 7;
+  const int before = x * q + (x < rem ? x : rem);
+  return before + local;
 }
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
@@ -181,17 +211,16 @@ hipError_t launch_rmsnorm(const TIN *x, const TW *gain, typename ActOf<TW>::type
 // rounded to fp32 (positions are fixed for the whole step, so one table serves all layers).
 hipError_t launch_rope_table(const int32_t *pos, const double *inv_freq, float2 *rot, int rows,
                              int half, hipStream_t s);
+// qkv holds nsl k-slices [rows, (H + 2 Hkv) hd] of the projection, summed here in order.
 template <typename TW>
-hipError_t launch_rope_kv(const float *qkv, typename ActOf<TW>::type *q_out,
+hipError_t launch_rope_kv(const float *qkv, int nsl, typename ActOf<TW>::type *q_out,
                           const TreeMeta &meta, TW *cache_k, TW *cache_v, int B, int n1, int H,
                           int Hkv, int hd, int capacity, const float2 *rot, hipStream_t s);
 
 
-enum GemmEpi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_QKV_ROPE = 4,
-               EPI_F32_MAX = 5 };
+enum GemmEpi { EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_QKV_ROPE = 4, EPI_F32_MAX = 5 };
 
 // C[M, N] = A[M, K] . W[N, K]^T with the epilogue:
-//  EPI_STORE : out (activation type) [M, N]
 //  EPI_RESID : resid (fp32) [M, N] += C
 //  EPI_SWIGLU: W holds 2F rows (gate, up); out[M, F] = silu(gate) * up, N = F
 //  EPI_F32   : outf (fp32) [M, N] = C
@@ -199,7 +228,8 @@ enum GemmEpi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_QK
 //              rows happen in the epilogue (see launch_qkv_rope)
 //  EPI_F32_MAX: as EPI_F32, and the maximum of every row over each column tile
 //              (see launch_lm_head)
-// A is in the activation type.  aux.part: fp32 workspace for split-K partials
+// A is in the activation type; fp16 activations (A, and the fp16 outputs) are laid out by
+// act_off, fp32 ones row-major.  aux.part: fp32 workspace for split-K partials
 // (aux.part_cap floats), aux.cus: compute units of the device.
 struct GemmAux {
   float *part;
@@ -260,8 +290,9 @@ hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 
 // fp16 MFMA-fragment order the packed GEMM path reads (same byte size).
 hipError_t launch_pack_weights(const bf16 *W, f16 *P, int rows, int K, hipStream_t s);
 
-// Exact widening of a bf16 tensor to fp16 (in range), n elements.
-hipError_t launch_cast_bf16_f16(const bf16 *in, f16 *out, size_t n, hipStream_t s);
+// Exact widening (in range) of a row-major bf16 matrix [rows, d] to fp16 in the
+// activation layout (act_off).
+hipError_t launch_cast_bf16_f16(const bf16 *in, f16 *out, int rows, int d, hipStream_t s);
 
 template <typename TW>
 hipError_t launch_attention(const typename ActOf<TW>::type *q, const TW *cache_k,

@@ -15,7 +15,7 @@
 // with per-tile row maxima for the vocabulary kernel), RoPE + q store + cache write of
 // the tree K/V (QKV projection), fp32 residual add followed by the next block's RMSNorm
 // (attention output and MLP down projections), SwiGLU (gate/up projection: each tile
-// holds matching gate and up columns), activation-type store.
+// holds matching gate and up columns).
 #include <cmath>
 
 #include "common.h"
@@ -30,14 +30,6 @@ template <> struct Vec8<f16> { typedef f16x8 type; };
 template <> struct Vec8<bf16> { typedef bf16x8 type; };
 AS_DEVICE f16x8 to_f16(f16x8 v) { return v; }
 AS_DEVICE f16x8 to_f16(bf16x8 v) { return bf16x8_to_f16x8(v); }
-
-// Maps a workgroup id onto a tile id so that consecutive tile ids share an XCD.
-AS_DEVICE int xcd_tile(int bid, int total) {
-  const int x = bid & 7, local = bid >> 3;
-  const int q = total >> 3, rem = total & 7;
-  const int before = x * q + (x < rem ? x : rem);
-  return before + local;
-}
 
 // ------------------------------------------------------------------------------------
 // fp16-activation MFMA kernel, templated on the tiling.
@@ -149,23 +141,26 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
   const int wm = wl / WNN, wn = wl - wm * WNN;
   const int lr = lane & 15, lk = lane >> 4;
 
-  // DMA sources: block j of an operand covers tile rows ROWS_PER_BLK*j ..; lane l lands at
-  // row ROWS_PER_BLK*j + l / PIECES, physical piece l % PIECES.  Rows of A past M get an
-  // offset past the end of A's buffer range, which the buffer load's range check turns
-  // into zeros (no fetch, and zero MFMA operands draw less power); rows of W past N are
-  // clamped to the last row.  Neither product is ever stored.
+  // DMA sources.  A: block j is the operand of tile row block j / KSUB at k step j % KSUB of
+  // the stage, one contiguous 1 KB run of the activation layout in lane order.  Rows of A
+  // past M get an offset past the end of A's buffer range, which the buffer load's range
+  // check turns into zeros (no fetch, and zero MFMA operands draw less power).  Row-major
+  // W: block j covers tile rows ROWS_PER_BLK*j ..; lane l lands at row ROWS_PER_BLK*j +
+  // l / PIECES, physical piece l % PIECES; rows of W past N are clamped to the last row.
+  // Neither product is ever stored.
   const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A, (uint32_t)((size_t)M * K * 2));
   const int wrows = EPI == acespec::EPI_SWIGLU ? 2 * N : N;
   const __amdgpu_buffer_rsrc_t rsb = make_rsrc(W, (uint32_t)((size_t)wrows * K * 2));
   const int drow = lane / PIECES, dpc = lane % PIECES;
   uint32_t va[A_DMA], vb[B_DMA > 0 ? B_DMA : 1];
+  int sa[A_DMA];  // bytes from one stage's k columns to the next in this block's rows
 #pragma unroll
   for (int t = 0; t < A_DMA; ++t) {
     const int blk = w * A_DMA + t < A_BLKS ? w * A_DMA + t : A_BLKS - 1;
-    const int lrow = blk * ROWS_PER_BLK + drow;
-    const int r = m0 + lrow;
-    va[t] = r < M ? (uint32_t)r * K * 2 + (piece_off<ROWB>(lrow, dpc) - lrow * ROWB)
-                  : (uint32_t)M * K * 2;
+    const int r0 = m0 + blk / KSUB * 16, rl = min(max(M - r0, 0), 16);
+    va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % KSUB * 4 + lk) * rl + lr) * 8) * 2
+                    : (uint32_t)M * K * 2;
+    sa[t] = rl * ROWB;
   }
 #pragma unroll
   for (int t = 0; t < B_DMA; ++t) {
@@ -201,15 +196,14 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
   }
   auto issue = [&](int kt, int stage) {
     char *base = smem + stage * STAGE_BYTES;
-    const int soff = kt * ROWB;
 #pragma unroll
     for (int t = 0; t < A_DMA; ++t) {
       const int blk = w * A_DMA + t < A_BLKS ? w * A_DMA + t : A_BLKS - 1;
-      buf_dma16(rsa, (lds_ptr_t)(base + blk * 1024), va[t], soff);
+      buf_dma16(rsa, (lds_ptr_t)(base + blk * 1024), va[t], kt * sa[t]);
     }
 #pragma unroll
     for (int t = 0; t < B_DMA; ++t)
-      buf_dma16(rsb, (lds_ptr_t)(base + A_BYTES + (w * B_DMA + t) * 1024), vb[t], soff);
+      buf_dma16(rsb, (lds_ptr_t)(base + A_BYTES + (w * B_DMA + t) * 1024), vb[t], kt * ROWB);
   };
 
   // Fragment byte offsets within a stage: A fragment f = (k step f / WTM, row block
@@ -217,7 +211,7 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
   int aoff[F], boff[KSUB][WTN];
 #pragma unroll
   for (int f = 0; f < F; ++f)
-    aoff[f] = piece_off<ROWB>(wm * WTM * 16 + (f % WTM) * 16 + lr, (f / WTM) * 4 + lk);
+    aoff[f] = ((wm * WTM + f % WTM) * KSUB + f / WTM) * 1024 + lane * 16;
 #pragma unroll
   for (int j = 0; j < WTN; ++j) {
     const int brow = (EPI == acespec::EPI_SWIGLU)
@@ -243,10 +237,9 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
     constexpr int L_VM = A_DMA + WTN;
     constexpr int FW = WTM;  // A fragments of this wave's k-step
     f16x8 rb[NST][WTN], fa[FW];
-    int aok[FW];  // this group's 16-byte pieces of the stage's rows
+    int aok[FW];  // this group's operands of the stage
 #pragma unroll
-    for (int f = 0; f < FW; ++f)
-      aok[f] = piece_off<ROWB>(wm * WTM * 16 + f * 16 + lr, kg * 4 + lk);
+    for (int f = 0; f < FW; ++f) aok[f] = ((wm * WTM + f) * KSUB + kg) * 1024 + lane * 16;
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p) {
       const int kt = kt0 + (p < nk ? p : nk - 1);
@@ -481,7 +474,7 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
         for (int jj = 0; jj < HALF; ++jj) {
           const int col = tn * (TBN / 2) + wn * HALF * 16 + jj * 16 + lr;
           if (col < N)
-            out[(size_t)row * N + col] = (f16)silu_mul(acc[ii][jj][e], acc[ii][jj + HALF][e]);
+            out[act_off(row, col, M, N)] = (f16)silu_mul(acc[ii][jj][e], acc[ii][jj + HALF][e]);
         }
       } else {
 #pragma unroll
@@ -489,8 +482,7 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
           const int col = tn * TBN + wn * WTN * 16 + j * 16 + lr;
           if (col >= N) continue;
           const size_t o = (size_t)row * N + col;
-          if (EPI == acespec::EPI_STORE) out[o] = (f16)acc[ii][j][e];
-          else if (EPI == acespec::EPI_RESID) outf[o] += acc[ii][j][e];
+          if (EPI == acespec::EPI_RESID) outf[o] += acc[ii][j][e];
           else outf[o] = acc[ii][j][e];
         }
       }
@@ -570,8 +562,7 @@ __global__ __launch_bounds__(256) void tile_fixup_kernel(const float *__restrict
     const int col = col0 + q;
     if (col >= N) continue;
     const size_t o = (size_t)row * N + col;
-    if (EPI == acespec::EPI_SWIGLU) out[o] = (f16)silu_mul(av[q], uv[q]);
-    else if (EPI == acespec::EPI_STORE) out[o] = (f16)av[q];
+    if (EPI == acespec::EPI_SWIGLU) out[act_off(row, col, M, N)] = (f16)silu_mul(av[q], uv[q]);
     else if (EPI == acespec::EPI_RESID) outf[o] += av[q];
     else outf[o] = av[q];
   }
@@ -587,7 +578,8 @@ __global__ __launch_bounds__(256) void fixup_resid_norm_kernel(
     const float *__restrict__ part, float *__restrict__ x, const TG *__restrict__ gain,
     f16 *__restrict__ out, int N, int mt, int tsplit, float eps) {
   constexpr int MAXJ = 8;
-  const int row = blockIdx.x, tid = threadIdx.x;
+  // neighbouring rows on one XCD: their pieces share lines of the activation layout
+  const int M = gridDim.x, row = xcd_tile(blockIdx.x, M), tid = threadIdx.x;
   const int tm = row / TBM, lrow = row - tm * TBM;
   const int n4 = N >> 2;
   float4 v[MAXJ];
@@ -618,7 +610,6 @@ __global__ __launch_bounds__(256) void fixup_resid_norm_kernel(
   __syncthreads();
   const float tot = (red[0] + red[1]) + (red[2] + red[3]);
   const float scale = 1.0f / sqrtf(tot / (float)N + eps);
-  f16 *o = out + (size_t)row * N;
 #pragma unroll
   for (int j = 0; j < MAXJ; ++j) {
     const int c = tid + 256 * j;
@@ -627,9 +618,273 @@ __global__ __launch_bounds__(256) void fixup_resid_norm_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) g[e] = (float)gain[4 * c + e];
       typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-      *(h4 *)(o + 4 * c) = h4{(f16)(v[j].x * scale * g[0]), (f16)(v[j].y * scale * g[1]),
+      *(h4 *)(out + act_off(row, 4 * c, M, N)) = h4{(f16)(v[j].x * scale * g[0]), (f16)(v[j].y * scale * g[1]),
                               (f16)(v[j].z * scale * g[2]), (f16)(v[j].w * scale * g[3])};
     }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Few rows (up to 288): the product is bound by the stream of the weights, so what it needs
+// is all CUs at it, enough bytes in flight on each, and little else through the CU's load
+// path, which moves one 128-byte line about every 4 clocks whatever the lines hold (1 KB
+// loads measured 29-33 clocks each, 16 half-used lines 72).  Tiles of MB * 16 rows x 128
+// columns, eight waves: four of 32 columns times two k groups (the two 32-wide steps of
+// each 64-wide unit).  The activations pass through LDS once for the 128 columns, no two
+// waves load the same weights, an A operand read from LDS feeds two MFMAs, and the k groups
+// halve the LDS reads a column costs.  NST - 1 units of weights and activations are in
+// flight, with one barrier a unit.  Packed weights go straight to registers; row-major ones
+// through LDS too, in whole 128-byte lines.
+//   out: EPI_SWIGLU writes the activation; EPI_F32_MAX the product and tmax[row][tn], the
+// row's maximum over the 128 columns; EPI_F32 fp32 sums to outf + slice * M * N.
+// ------------------------------------------------------------------------------------
+constexpr int ROWSN = 128;
+template <int EPI, int PK, int MB, int NST>
+__global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict__ A,
+                                                           const void *__restrict__ W, int M,
+                                                           int N, int K, f16 *__restrict__ out,
+                                                           float *__restrict__ outf, int mt,
+                                                           int nt, int nsl,
+                                                           float *__restrict__ tmax) {
+  constexpr bool SW = EPI == acespec::EPI_SWIGLU;
+  constexpr int WTN = 2, TBM = MB * 16;
+  constexpr int A_BYTES = MB * 2048, STAGE = A_BYTES + (PK ? 0 : ROWSN * 128);
+  constexpr int ABLK = MB * 2, A_DMA = (ABLK + 7) / 8;
+  constexpr int L_VM = A_DMA + 2;             // loads a wave issues per unit
+  constexpr int MBH = (MB + 1) / 2;           // row blocks finished by k group 0
+  constexpr int RED = 8 * MBH * WTN * 4 * 64 * 4;
+  constexpr int RING = NST * STAGE + 1024;    // (and 1 KB where surplus DMA lands)
+  __shared__ __attribute__((aligned(1024))) char smem[RING > RED ? RING : RED];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = w >> 2, wn = w & 3;
+  const int lr = lane & 15, lk = lane >> 4;
+  // row tiles of one weight panel run side by side on one XCD, k-slices outermost
+  const int u = xcd_tile(blockIdx.x, mt * nt * nsl);
+  const int sl = u / (mt * nt), tile = u - sl * mt * nt, tn = tile / mt, tm = tile - tn * mt;
+  const int m0 = tm * TBM;
+  const int U = K >> 6;
+  const int u0 = (int)((long long)U * sl / nsl), u1 = (int)((long long)U * (sl + 1) / nsl);
+
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A, (uint32_t)((size_t)M * K * 2));
+  uint32_t va[A_DMA];
+  int sa[A_DMA], lb[A_DMA];
+#pragma unroll
+  for (int t = 0; t < A_DMA; ++t) {
+    // every wave issues A_DMA loads a unit, so that one vmcnt holds for all; a surplus one
+    // is out of the buffer's range: nothing is fetched, zeros land in the spare 1 KB
+    const int blk = w + t * 8;
+    const int r0 = m0 + blk / 2 * 16, rl = blk < ABLK ? min(max(M - r0, 0), 16) : 0;
+    va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2
+                    : (uint32_t)M * K * 2;
+    sa[t] = rl * 128;
+    lb[t] = blk * 1024;
+  }
+  // Weights, as a buffer over the tile's panel (two panels for SwiGLU: gate, up).  Packed:
+  // this wave's two 16-row blocks at k step kg.  Row-major: 8-row x 128-byte blocks 2 w and
+  // 2 w + 1 of the tile's 128 rows; rows past N repeat the last one.
+  const int c0 = SW ? tn * (ROWSN / 2) : tn * ROWSN;
+  const int npan = SW ? ROWSN / 2 : ROWSN, nrows = min(npan, N - c0);
+  const char *wbase = (const char *)W + (size_t)c0 * K * 2;
+  const uint32_t wbytes = (uint32_t)nrows * K * 2;
+  const __amdgpu_buffer_rsrc_t rsw[2] = {
+      make_rsrc(wbase, wbytes), make_rsrc(wbase + (SW ? (size_t)N * K * 2 : 0), wbytes)};
+  uint32_t vw[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (PK) {
+      const int c = min(SW ? wn * 16 : wn * 32 + j * 16, nrows - 16);
+      vw[j] = (uint32_t)c * K * 2 + kg * 1024 + lane * 16;
+    } else {
+      const int row = (w * 2 + j) * 8 + (lane >> 3), r = SW ? row & 63 : row;
+      vw[j] = (uint32_t)min(r, nrows - 1) * K * 2 + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+  }
+  // (SwiGLU's panel: by the block in the packed form, by the wave in the row-major form)
+  const __amdgpu_buffer_rsrc_t rsp = rsw[SW && !PK && w >= 4];
+  u32x4 rb[PK ? NST : 1][WTN];
+  f16x8 fa[MB];
+  auto issue = [&](int unit, int st) {
+#pragma unroll
+    for (int t = 0; t < A_DMA; ++t)
+      buf_dma16(rsa,
+                (lds_ptr_t)(smem + (w + t * 8 < ABLK ? st * STAGE + lb[t] : NST * STAGE)), va[t],
+                unit * sa[t]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (PK)
+        rb[st][j] = buf_load16<true>(rsw[SW ? j : 0], vw[j], unit * 2048);
+      else
+        buf_dma16_stream(rsp, (lds_ptr_t)(smem + st * STAGE + A_BYTES + (w * 2 + j) * 1024),
+                         vw[j], unit * 128);
+    }
+  };
+  int boff[WTN];   // row-major: this wave's weight operands in a stage
+#pragma unroll
+  for (int j = 0; j < WTN; ++j)
+    boff[j] = A_BYTES + piece_off<128>((SW ? j * 64 + wn * 16 : wn * 32 + j * 16) + lr, kg * 4 + lk);
+  f32x4 acc[MB][WTN];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nk = u1 - u0;
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) issue(u0 + min(p, nk - 1), p);
+  auto step = [&](int i, int s) {
+    wait_vmcnt<(NST - 2) * L_VM>();
+    __builtin_amdgcn_s_barrier();
+    const char *sc = smem + s * STAGE + kg * 1024 + lane * 16;
+    f16x8 b[WTN];
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) {
+      if constexpr (PK) b[j] = __builtin_bit_cast(f16x8, rb[s][j]);
+      else b[j] = bf16x8_to_f16x8(*(const bf16x8 *)(smem + s * STAGE + boff[j]));
+    }
+    fa[0] = *(const f16x8 *)sc;
+    if constexpr (MB > 1) fa[1] = *(const f16x8 *)(sc + 2048);
+    if constexpr (MB > 2) fa[2] = *(const f16x8 *)(sc + 4096);
+#pragma unroll
+    for (int f = 0; f < MB; ++f) {
+      if (f + 3 < MB) fa[f + 3] = *(const f16x8 *)(sc + (f + 3) * 2048);
+      SCHED_FENCE();
+#pragma unroll
+      for (int j = 0; j < WTN; ++j)
+        acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[f], b[j], acc[f][j], 0, 0, 0);
+      SCHED_FENCE();
+      if (f == 0) issue(u0 + min(i + NST - 1, nk - 1), (s + NST - 1) % NST);
+    }
+  };
+  int i0 = 0;
+  wait_lgkmcnt0();
+  for (; i0 + NST <= nk; i0 += NST) {
+#pragma unroll
+    for (int s = 0; s < NST; ++s) step(i0 + s, s);
+  }
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (i0 + s < nk) step(i0 + s, s);
+  wait_vmcnt<0>();
+
+  // the k groups swap halves: group 0 finishes row blocks 0 .. MBH - 1, group 1 the rest
+  __syncthreads();
+  float *red = (float *)smem + (size_t)w * (MBH * WTN * 4 * 64);
+  const float *other = (const float *)smem + (size_t)(w ^ 4) * (MBH * WTN * 4 * 64);
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+    if ((i >= MBH) == (kg == 0)) {
+#pragma unroll
+      for (int j = 0; j < WTN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          red[(((i >= MBH ? i - MBH : i) * WTN + j) * 4 + e) * 64 + lane] = acc[i][j][e];
+    }
+  __syncthreads();
+  if constexpr (EPI != acespec::EPI_F32_MAX) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if ((i >= MBH) != (kg == 1)) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = m0 + i * 16 + lk * 4 + e;
+        float v[WTN];
+#pragma unroll
+        for (int j = 0; j < WTN; ++j)
+          v[j] = acc[i][j][e] + other[(((i >= MBH ? i - MBH : i) * WTN + j) * 4 + e) * 64 + lane];
+        if (row >= M) continue;
+        if constexpr (SW) {
+          const int col = tn * (ROWSN / 2) + wn * 16 + lr;
+          if (col < N) out[act_off(row, col, M, N)] = (f16)silu_mul(v[0], v[1]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < WTN; ++j) {
+            const int col = tn * ROWSN + wn * 32 + j * 16 + lr;
+            if (col < N) outf[((size_t)sl * M + row) * N + col] = v[j];
+          }
+        }
+      }
+    }
+  } else {
+    // the product, and per row its maximum over the tile's columns (padding columns repeat
+    // a real one; a non-finite value makes it +inf)
+    __shared__ float mx[4][TBM];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if ((i >= MBH) != (kg == 1)) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int lrow = i * 16 + lk * 4 + e, row = m0 + lrow;
+        float m = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) {
+          const float v =
+              acc[i][j][e] + other[(((i >= MBH ? i - MBH : i) * WTN + j) * 4 + e) * 64 + lane];
+          m = max_or_inf(m, v);
+          const int col = tn * ROWSN + wn * 32 + j * 16 + lr;
+          if (row < M && col < N) outf[(size_t)row * N + col] = v;
+        }
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        if (lr == 0) mx[wn][lrow] = m;
+      }
+    }
+    __syncthreads();
+    if (tid < TBM && m0 + tid < M)
+      tmax[(size_t)(m0 + tid) * nt + tn] =
+          fmaxf(fmaxf(mx[0][tid], mx[1][tid]), fmaxf(mx[2][tid], mx[3][tid]));
+  }
+}
+
+// The same for gemm_rows_kernel's sums: part holds nsl k-slices [M, N].  With few rows the
+// kernel is a chain of memory latencies, so a row gets up to 1024 threads with one or two
+// float4 columns each, and the loads of four slices at a time are issued together (256
+// threads and one load after the other took 16 us at 138 rows of 4096 in eight slices).
+template <typename TG, int J>
+__global__ __launch_bounds__(1024) void rows_resid_norm_kernel(
+    const float *__restrict__ part, float *__restrict__ x, const TG *__restrict__ gain,
+    f16 *__restrict__ out, int N, int nsl, float eps) {
+  const int M = gridDim.x, row = xcd_tile(blockIdx.x, M), tid = threadIdx.x, T = blockDim.x;
+  const int n4 = N >> 2;
+  const size_t slice = (size_t)M * N;
+  float4 v[J];
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = tid + T * j;
+    if (c >= n4) break;
+    const float *pt = part + (size_t)row * N + 4 * c;
+    float4 *xp = (float4 *)(x + (size_t)row * N) + c;
+    float4 t = *xp, a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < nsl; s0 += 4) {
+      float4 w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[q] = *(const float4 *)(pt + min(s0 + q, nsl - 1) * slice);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (s0 + q < nsl) { a.x += w[q].x; a.y += w[q].y; a.z += w[q].z; a.w += w[q].w; }
+    }
+    t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w;
+    *xp = t;
+    v[j] = t;
+    ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
+  }
+  __shared__ float red[16];
+  ss = wave_sum(ss);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+  for (int q = 0; q < T / 64; ++q) tot += red[q];
+  const float scale = 1.0f / sqrtf(tot / (float)N + eps);
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = tid + T * j;
+    if (c >= n4) break;
+    typedef TG g4 __attribute__((ext_vector_type(4)));
+    const g4 g = *(const g4 *)(gain + 4 * c);
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    *(h4 *)(out + act_off(row, 4 * c, M, N)) =
+        h4{(f16)(v[j].x * scale * (float)g[0]), (f16)(v[j].y * scale * (float)g[1]),
+           (f16)(v[j].z * scale * (float)g[2]), (f16)(v[j].w * scale * (float)g[3])};
   }
 }
 
@@ -700,7 +955,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
       if (col >= N) continue;
       const size_t o = (size_t)row * N + col;
       if (EPI == acespec::EPI_SWIGLU) out[o] = silu_mul(acc[i][j], acc[i][4 + j]);
-      else if (EPI == acespec::EPI_STORE) out[o] = acc[i][j];
       else if (EPI == acespec::EPI_RESID) outf[o] += acc[i][j];
       else outf[o] = acc[i][j];
     }
@@ -724,7 +978,6 @@ __global__ __launch_bounds__(256) void pack_frag_kernel(const bf16 *__restrict__
   *(f16x8 *)(P + u * 8) = bf16x8_to_f16x8(v);
 }
 
-using acespec::EPI_STORE;
 using acespec::EPI_RESID;
 using acespec::EPI_SWIGLU;
 using acespec::EPI_F32;
@@ -870,6 +1123,74 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
   return 0;
 }
 
+// gemm_rows_kernel's tiling: row tiles of up to 144 rows, as few and as low as hold M, and
+// the k-slices of the fp32 products.  A slice saves k units (about 0.35 + 0.03 mb us each,
+// one workgroup a CU) and costs its fp32 sums' round trip (about 3.5 TB/s).
+struct RowsPlan {
+  int mb, mt, nt, nsl;
+};
+RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap) {
+  RowsPlan p;
+  p.mt = (M + 143) / 144;
+  const int blocks = (M + 16 * p.mt - 1) / (16 * p.mt);
+  p.mb = blocks <= 3 ? blocks : blocks <= 5 ? 5 : blocks <= 7 ? 7 : 9;
+  p.nt = epi == EPI_SWIGLU ? (N + ROWSN / 2 - 1) / (ROWSN / 2) : (N + ROWSN - 1) / ROWSN;
+  p.nsl = 1;
+  if (epi == EPI_F32) {
+    const int U = K / 64;
+    const double unit = 0.35 + 0.03 * p.mb, sums = (double)M * N * 8 / 3.5e6;
+    double best = 1e30;
+    for (int n = 1; n <= 8; ++n) {
+      if (n > 1 && (n * p.mt * p.nt > cus || U / n < 4 || (long long)n * M * N > cap)) break;
+      const double t = (U + n - 1) / n * unit + n * sums;
+      if (t < best) { best = t; p.nsl = n; }
+    }
+  }
+  return p;
+}
+// Where it runs.  Against the 128 x 128, 288 x 64 and 128 x 256 tiles it takes the place of
+// (8B / 1B shapes, us): gate/up at 138 rows 47 for 87 (packed) and 52 for 142 (row-major),
+// at 272 rows 25 for 31 (1B); beyond 288 rows the larger tiles are faster (packed, 384 rows:
+// 98 against 114).  The residual products keep it longer (down at 520 rows: 77 for 97
+// row-major), but for the packed 8B-class ones from 289 rows (432: 79 against 71).
+constexpr int kFewRows = 288, kSomeRows = 544;
+bool rows_ok(int epi, int M, int N, int K, int packed) {
+  if (K % 64 != 0 || N % 16 != 0) return false;
+  if (epi == EPI_RESID && M <= kSomeRows && !(packed && (long long)N * K > (32 << 20)))
+    return true;
+  // the LM head's row-major panels leave LDS for one workgroup a CU beyond 48 rows, whose
+  // logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128 tiles)
+  if (epi == EPI_F32_MAX) return M <= (packed ? 144 : 48);
+  return M <= kFewRows;
+}
+
+template <int EPI>
+void launch_rows(hipStream_t s, const f16 *A, const bf16 *W, int M, int N, int K, f16 *out,
+                 float *outf, const RowsPlan &p, int packed, float *tmax = nullptr) {
+#define ROWS(MB, NST)                                                                        \
+  case MB:                                                                                   \
+    if (packed)                                                                              \
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, MB, NST>), grid, dim3(512), 0, s, A, W, M,  \
+                         N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                          \
+    else                                                                                     \
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, 0, MB, EPI == EPI_F32_MAX && MB <= 5 ? 3 : 4>), grid, dim3(512), 0, s, A, W, M,    \
+                         N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                          \
+    break
+  const dim3 grid(p.mt * p.nt * p.nsl);
+  switch (p.mb) {
+    ROWS(1, 5); ROWS(2, 5); ROWS(3, 5); ROWS(5, 5); ROWS(7, 5); ROWS(9, 5);
+    default: break;
+  }
+#undef ROWS
+}
+
+void launch_rows_resid_norm(hipStream_t s, const float *part, float *x, const bf16 *gain,
+                            f16 *out, int M, int N, int nsl, float eps) {
+  const int threads = N >= 4096 ? 1024 : (N / 4 + 63) / 64 * 64;   // N <= 8192
+  auto kernel = N > 4 * threads ? rows_resid_norm_kernel<bf16, 2> : rows_resid_norm_kernel<bf16, 1>;
+  hipLaunchKernelGGL(kernel, dim3(M), dim3(threads), 0, s, part, x, gain, out, N, nsl, eps);
+}
+
 }  // namespace
 
 namespace acespec {
@@ -892,7 +1213,6 @@ hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 
            (long long)tiles * splits_override * tbm * tbn <= part_cap)
     sp = SplitPlan{0, splits_override};
   switch (epi) {
-    case EPI_STORE: launch_epi<EPI_STORE, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp); break;
     case EPI_RESID: launch_epi<EPI_RESID, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp); break;
     case EPI_SWIGLU: launch_epi<EPI_SWIGLU, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp); break;
     default: launch_epi<EPI_F32, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp);
@@ -913,6 +1233,13 @@ template <>
 hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, int K,
                                              float *x, const bf16 *gain, f16 *out, float eps,
                                              const GemmAux &aux, hipStream_t s) {
+  if (rows_ok(EPI_RESID, M, N, K, aux.packed) && N <= 8 * 4 * 256 &&
+      (long long)M * N <= aux.part_cap) {
+    const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
+    launch_rows<EPI_F32>(s, A, W, M, N, K, nullptr, aux.part, mp, aux.packed);
+    launch_rows_resid_norm(s, aux.part, x, gain, out, M, N, mp.nsl, eps);
+    return hipGetLastError();
+  }
   const int var = pick_variant(EPI_RESID, M, N, K, aux.packed);
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
@@ -960,6 +1287,11 @@ hipError_t launch_pack_weights(const bf16 *W, f16 *P, int rows, int K, hipStream
 template <>
 hipError_t launch_gemm<bf16, f16>(int epi, const f16 *A, const bf16 *W, int M, int N, int K,
                                   f16 *out, float *outf, const GemmAux &aux, hipStream_t s) {
+  if (epi == EPI_SWIGLU && rows_ok(epi, M, N, K, aux.packed)) {
+    launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, nullptr,
+                           plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0), aux.packed);
+    return hipGetLastError();
+  }
   return launch_f16w_variant<bf16>(-1, 0, epi, A, W, M, N, K, out, outf, aux.part,
                                    aux.part_cap, aux.cus, s, aux.packed);
 }
@@ -970,10 +1302,6 @@ hipError_t launch_gemm<float, float>(int epi, const float *A, const float *W, in
                                      hipStream_t s) {
   const dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
   switch (epi) {
-    case EPI_STORE:
-      hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, grid, block, 0, s, A, W, M, N, K, out,
-                         outf);
-      break;
     case EPI_RESID:
       hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, s, A, W, M, N, K, out,
                          outf);
@@ -1006,6 +1334,15 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
   // cache write stay in the epilogue (measured level with the separate RoPE kernel after
   // a split product, and with eight 64 x 64 waves a tile)
   const bool fusable = N == (ro.H + 2 * ro.Hkv) * ro.hd;
+  if (rows_ok(EPI_F32, M, N, K, aux.packed)) {
+    const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
+    float *dst = mp.nsl > 1 ? aux.part : qkv;
+    launch_rows<EPI_F32>(s, A, W, M, N, K, nullptr, dst, mp, aux.packed);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_rope_kv<bf16>(dst, mp.nsl, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv,
+                                ro.hd, ro.capacity, ro.rot, s);
+  }
   if (aux.packed && M > 384 && fusable && 128 % ro.hd == 0) {
     // tiles kept whole, each with two wave groups splitting its k-steps (two waves a SIMD
     // with about one tile a CU), RoPE and cache write in the epilogue: 112 x 256 tiles from
@@ -1035,7 +1372,7 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
   hipError_t e = launch_f16w_variant<bf16>(var, 0, EPI_F32, A, W, M, N, K, nullptr, qkv,
                                            aux.part, aux.part_cap, aux.cus, s, aux.packed);
   if (e != hipSuccess) return e;
-  return launch_rope_kv<bf16>(qkv, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
+  return launch_rope_kv<bf16>(qkv, 1, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
                               ro.capacity, ro.rot, s);
 }
 
@@ -1046,7 +1383,7 @@ hipError_t launch_qkv_rope<float, float>(const float *A, const float *W, int M, 
                                          hipStream_t s) {
   hipError_t e = launch_gemm<float, float>(EPI_F32, A, W, M, N, K, nullptr, qkv, aux, s);
   if (e != hipSuccess) return e;
-  return launch_rope_kv<float>(qkv, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
+  return launch_rope_kv<float>(qkv, 1, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
                                ro.capacity, ro.rot, s);
 }
 
@@ -1055,6 +1392,12 @@ hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, 
                                      float *logits, float *tile_max, int *ntile,
                                      const GemmAux &aux, hipStream_t s) {
   *ntile = 0;
+  if (tile_max && rows_ok(EPI_F32_MAX, M, N, K, aux.packed)) {
+    const RowsPlan mp = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0);
+    launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, nullptr, logits, mp, aux.packed, tile_max);
+    *ntile = mp.nt;
+    return hipGetLastError();
+  }
   const int var = pick_variant(EPI_F32, M, N, K, aux.packed);
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;

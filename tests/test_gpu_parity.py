@@ -84,6 +84,21 @@ def test_tree_small_bf16_packed_weights(variant):
     _check_tree(run, tol=2e-2)
 
 
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("B, depth, d, F", [
+    (1, 0, 320, 576), (1, 15, 320, 576), (1, 16, 1024, 2048), (3, 15, 320, 576),
+    (7, 6, 320, 576), (1, 64, 1024, 2048), (5, 15, 320, 576), (7, 15, 320, 576),
+    (9, 15, 1024, 2048), (5, 28, 320, 576), (9, 31, 1024, 2048), (17, 16, 320, 576),
+    (17, 31, 320, 576), (5, 54, 2048, 4096)])
+def test_tree_row_counts(B, depth, d, F, packed):
+    """Batches of B * (depth + 1) rows at the edges of the few-row GEMM's row tiles (1 to 9
+    row blocks, a second row tile, the last rows it takes and the first it does not), with
+    few and many k units and k-slices, and partial row blocks of the activation layout."""
+    w = small_bf16(d=d, F=F, B=B, S=40, tree="chain", depth=depth, V=5008 if packed else 5004)
+    run = hz.run_tree(w, packed=packed)
+    _check_tree(run, tol=2e-2)
+
+
 def test_pack_weight_layout_matches_its_definition():
     """acespec_pack_weight against the layout written out on the host: 16-byte unit
     u = (nb * cols/32 + kt) * 64 + l holds row nb*16 + l%16, columns kt*32 + (l/16)*8 .. +8,
