@@ -7,6 +7,7 @@
 // + SwiGLU, down GEMM + residual} -> final RMSNorm -> LM head GEMM (fp32 logits) ->
 // fused vocabulary verify -> path walk.  Everything is enqueued on the caller's stream
 // without synchronisation and without allocation.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -65,6 +66,8 @@ struct acespec_ctx {
   float2 *rot = nullptr;      // RoPE (cos, sin) per tree row and frequency, per step
   float *tile_max = nullptr;  // LM-head row maxima per column tile
   uint32_t *cand = nullptr;   // vocabulary kernel: threshold-bin candidates per row
+  void *vsplit = nullptr;     // vocabulary kernels: scratch for splitting few rows
+  size_t vsplit_bytes = 0;
   int32_t *rowflag = nullptr; // vocabulary kernel: per-row data-error code (0 = none)
   TreeMeta meta{};
   // timing
@@ -213,6 +216,8 @@ int verify_tree_impl(acespec_ctx *ctx, const acespec_weights *w, const acespec_k
   va.ntile = ntile;
   va.cand = ctx->cand;
   va.cand_cap = kCandCap;
+  va.split = ctx->vsplit;
+  va.split_bytes = ctx->vsplit_bytes;
   va.rowflag = ctx->rowflag;
   va.u = uniforms;
   va.tok = meta.tok;
@@ -245,6 +250,8 @@ struct TailWorkspace {
   int32_t *rowflag;   // [R]
   void *a;            // [R, d_model] activation type: normalised / widened hidden states
   GemmAux aux;        // split-K partials (part_cap 0: the LM head is never split)
+  void *vsplit;       // the vocabulary kernels' row-splitting scratch, or NULL
+  size_t vsplit_bytes;
 };
 
 // ctx only times the launches (NULL: no timing).
@@ -277,6 +284,8 @@ int verify_tail_run(acespec_ctx *ctx, const acespec_model_desc &d, const TailWor
   va.ntile = ntile;
   va.cand = ws.cand;
   va.cand_cap = ws.cand_cap;
+  va.split = ws.vsplit;
+  va.split_bytes = ws.vsplit_bytes;
   va.rowflag = ws.rowflag;
   va.u = uniforms;
   va.tok = draft;
@@ -306,7 +315,8 @@ int verify_tail_impl(acespec_ctx *ctx, const void *lm_head, int packed, const vo
                      const float *uniforms, int R, int chain_len, const acespec_params *p,
                      const acespec_outputs *o, hipStream_t stream) {
   const TailWorkspace ws{ctx->logits, ctx->tile_max, ctx->cand, kCandCap, ctx->rowflag, ctx->a,
-                         GemmAux{ctx->gpart, ctx->gpart_cap, ctx->cus, packed}};
+                         GemmAux{ctx->gpart, ctx->gpart_cap, ctx->cus, packed}, ctx->vsplit,
+                         ctx->vsplit_bytes};
   return verify_tail_run<T>(ctx, ctx->d, ws, lm_head, final_norm, hidden, draft, draft_q,
                             uniforms, R, chain_len, p, o, stream);
 }
@@ -353,6 +363,9 @@ int acespec_create(const acespec_model_desc *desc, int max_batch, int max_nodes,
   const bool layers = d.n_layers > 0;
   const int G = layers ? d.n_heads / d.n_kv_heads : 1;
   const size_t QR = (size_t)G * (max_nodes + 1);
+  // (a call's chunks times rows, and so its scratch, is not monotone in its rows)
+  for (int r = 1; r <= c->max_rows && r <= kVocabSplitRows; ++r)
+    c->vsplit_bytes = std::max(c->vsplit_bytes, vocab_split_bytes(r, d.vocab));
   c->part_cap = layers ? ((long long)max_batch * d.n_kv_heads + 512) * QR * d.head_dim : 0;
   struct Part { size_t bytes; void **dst; };
   void *p_x = nullptr, *p_logits = nullptr, *p_po = nullptr, *p_pml = nullptr, *p_if = nullptr;
@@ -371,6 +384,7 @@ int acespec_create(const acespec_model_desc *desc, int max_batch, int max_nodes,
       {R * (size_t)((d.vocab + 127) / 128) * 4, &p_tmax},
       {R * (size_t)kCandCap * 4, &p_cand},
       {R * 4, &p_rflag},
+      {c->vsplit_bytes, &c->vsplit},
       {(size_t)c->part_cap * 4, &p_po},
       {(size_t)c->part_cap / (layers ? d.head_dim : 1) * 2 * 4, &p_pml},
       {layers ? (size_t)d.head_dim / 2 * 8 : 0, &p_if},
@@ -777,13 +791,17 @@ int acespec_verify_tail_noalloc(const acespec_model_desc *desc, const void *lm_h
   rc = scratch_of_current_device(&base, &cus);
   if (rc) return rc;
   const bool cand = need + b_cand <= kScratchBytes;
+  const size_t used = need + (cand ? b_cand : 0), b_split = vocab_split_bytes(R, d.vocab);
+  const bool split = b_split && used + b_split <= kScratchBytes;
   TailWorkspace ws{nullptr,
                    (float *)(base + b_flag),
                    cand ? (uint32_t *)(base + need) : nullptr,
                    cand ? kCandCap : 0,
                    (int32_t *)base,
                    need_a ? (void *)(base + b_flag + b_tmax) : nullptr,
-                   GemmAux{nullptr, 0, cus, lm_head_layout == ACESPEC_LAYOUT_PACKED ? 1 : 0}};
+                   GemmAux{nullptr, 0, cus, lm_head_layout == ACESPEC_LAYOUT_PACKED ? 1 : 0},
+                   split ? (void *)(base + used) : nullptr,
+                   split ? b_split : 0};
   if (d.dtype == ACESPEC_BF16)
     return verify_tail_run<bf16>(nullptr, d, ws, lm_head, final_norm, hidden, draft_tokens,
                                  draft_q, uniforms, R, chain_len, p, o, stream);

@@ -309,6 +309,9 @@ struct VocabArgs {
   int ntile;
   uint32_t *cand;           // [rows, cand_cap] scratch for threshold-bin candidates, or NULL
   int cand_cap;
+  void *split = nullptr;    // scratch of the row-splitting kernels (vocab_split_bytes), or NULL
+  size_t split_bytes = 0;
+  int chunks = 1;           // (set by launch_vocab)
   int32_t *rowflag;         // [rows] out: 0, ACESPEC_EBADDRAFT or ACESPEC_ENONFINITE
   const float *u;           // [rows, 3]
   const int32_t *tok;       // [rows] token of each row (children look theirs up here)
@@ -328,6 +331,10 @@ struct VocabArgs {
   float *topk_probs;
 };
 hipError_t launch_vocab(const VocabArgs &a, hipStream_t s);
+// Rows up to which a row's passes are split over several workgroups, and the scratch that
+// takes (0: not split).
+constexpr int kVocabSplitRows = 512;
+size_t vocab_split_bytes(int rows, int V);
 
 // The walk also folds the rows' data-error codes (rowflag) into status[b] of sessions
 // whose tree was valid.

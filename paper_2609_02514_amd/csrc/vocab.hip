@@ -40,9 +40,24 @@ constexpr int KMAX = 256;
 
 typedef unsigned long long u64;
 
-struct VSmem {
+// Block-wide scans and selections.
+struct VScan {
+  u64 wsum[NWV];
+  float wmax[NWV];
+  u64 above_p;             // selection results
+  uint32_t above_k;
+  int sel_p, sel_k;
+};
+// The top-k ids found by a segment pass.
+struct VTop {
+  uint32_t cand_key[KMAX];
+  int32_t cand_id[KMAX];
+  uint32_t cand_in[KMAX];
+  uint32_t ncand;
+};
+struct VSmem : VScan, VTop {
   // The threshold histograms (passes 1-3) and the per-segment tables (tie pass, pass 4)
-  // are never live together; sharing their storage keeps two rows in flight per CU.
+  // are never live together; sharing their storage keeps three rows in flight per CU.
   union {
     struct {  // pass 1: bits 31..20 of the key
       uint32_t cnt[4096];
@@ -60,18 +75,7 @@ struct VSmem {
       uint32_t tie_k[SEGMAX];
     } g;
   };
-  u64 wsum[NWV];
-  uint32_t wsum32[NWV];
-  float wmax[NWV];
-  uint32_t cand_key[KMAX];
-  int32_t cand_id[KMAX];
-  uint32_t cand_in[KMAX];
-  uint32_t ncand;
   uint32_t nbin;           // elements of the selected top-p / top-k bins (pass 2)
-  // selection results
-  u64 above_p;
-  uint32_t above_k;
-  int sel_p, sel_k;
   int flag;                // data-error code of the row (0 = none)
 };
 
@@ -85,7 +89,7 @@ AS_DEVICE float key_to_f32(uint32_t key) {  // inverse of f32_key
 }
 
 // Block-wide exclusive scan (u64).  All threads must call it.
-AS_DEVICE u64 block_scan_excl(u64 v, VSmem &sm, u64 &total) {
+AS_DEVICE u64 block_scan_excl(u64 v, VScan &sm, u64 &total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   u64 x = v;
 #pragma unroll
@@ -107,13 +111,13 @@ AS_DEVICE u64 block_scan_excl(u64 v, VSmem &sm, u64 &total) {
   return off + x - v;
 }
 
-AS_DEVICE u64 block_sum(u64 v, VSmem &sm) {
+AS_DEVICE u64 block_sum(u64 v, VScan &sm) {
   u64 t;
   block_scan_excl(v, sm, t);
   return t;
 }
 
-AS_DEVICE float block_max(float v, VSmem &sm) {
+AS_DEVICE float block_max(float v, VScan &sm) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   v = wave_max(v);
   if (lane == 0) sm.wmax[wave] = v;
@@ -130,7 +134,7 @@ AS_DEVICE float block_max(float v, VSmem &sm) {
 // count first reaches `target` (count mode); returns the bin and the amount strictly
 // above it.  nb is 4096, 2048 or 512.
 template <bool MASS>
-AS_DEVICE void select_bin(VSmem &sm, const uint32_t *cnt, const u64 *mass, int nb, u64 target,
+AS_DEVICE void select_bin(VScan &sm, const uint32_t *cnt, const u64 *mass, int nb, u64 target,
                           u64 base, int &sel, u64 &above) {
   const int t = threadIdx.x;
   if (t == 0) {  // defined result even if no bin qualifies (cannot happen for valid sums)
@@ -331,7 +335,452 @@ struct RowStream {
   }
 };
 
+// Segments [sb, se) of a row, one wave a segment: the fixed-point masses of p_r (seg_p) and
+// of the residual (seg_r, when resid), and the top-k ids, appended to sm.cand_*.  tie_base
+// gives the number of ids tied at the two thresholds before a segment (asked for only where
+// ids are tied).  Every draft probability read is checked: returns whether this thread saw a
+// NaN, infinite or negative one.  The VU segments of a step are loaded before any is used;
+// past the end of the row the last float4 is loaded again (unconditional loads), those lanes
+// are not valid.
+template <typename TieBase>
+AS_DEVICE bool segment_pass(const float *z, const float *q, int V, int sb, int se, bool resid,
+                            const Sel &sel, VTop &sm, TieBase tie_base, u64 *seg_p, u64 *seg_r) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  bool badq = false;
+  for (int s0 = sb + wave; s0 < se; s0 += NWV * VU) {
+    float4 z4u[VU], q4u[VU];
+#pragma unroll
+    for (int u = 0; u < VU; ++u) {
+      const int id0 = (s0 + u * NWV) * SEG + lane * 4;
+      const int ld = id0 < V ? id0 : V - 4;
+      // last pass over the row and its draft q: streamed past L2 and the MALL (the
+      // earlier passes keep the default policy, so their re-reads may hit the MALL)
+      z4u[u] = ld_stream(z + ld);
+      q4u[u] = resid ? ld_stream(q + ld) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < VU; ++u) {
+      const int s = s0 + u * NWV;
+      if (s >= se) break;
+      const int id0 = s * SEG + lane * 4;
+      const bool valid = id0 < V;
+      const float4 z4 = z4u[u], q4 = q4u[u];
+      const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
+      const float qq[4] = {q4.x, q4.y, q4.z, q4.w};
+      uint32_t key[4], rp[4], rk[4], tp = 0, tk = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) key[j] = f32_key(zz[j]);
+      if (sel.c_p > 1 || sel.c_k > 1) tie_base(s, tp, tk);
+      if (sel.c_p > 1) tie_ranks(key, valid, sel.tau_p, tp, rp);
+      else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rp[j] = 0;
+      }
+      if (sel.c_k > 1) tie_ranks(key, valid, sel.tau_k, tk, rk);
+      else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rk[j] = 0;
+      }
+      u64 sp_ = 0, sr_ = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (!valid) continue;
+        const bool inn = in_nucleus(key[j], rp[j], sel);
+        const float p = elem_p(zz[j], inn, sel);
+        sp_ += fixw(p);
+        if (resid) {
+          badq |= !(qq[j] >= 0.f && qq[j] <= 3.402823466e38f);
+          sr_ += fixw(fmaxf(p - qq[j], 0.f));
+        }
+        if (in_topk(key[j], rk[j], sel)) {
+          const uint32_t slot = atomicAdd(&sm.ncand, 1u);
+          if (slot < KMAX) {
+            sm.cand_key[slot] = key[j];
+            sm.cand_id[slot] = id0 + j;
+            sm.cand_in[slot] = inn ? 1u : 0u;
+          }
+        }
+      }
+      sp_ = wave_sum_u64(sp_);
+      sr_ = wave_sum_u64(sr_);
+      if (lane == 0) {
+        seg_p[s] = sp_;
+        seg_r[s] = sr_;
+      }
+    }
+  }
+  return badq;
+}
+
+// The largest mass target of the nucleus: ceil(top_p * S), within [1, S].
+AS_DEVICE u64 nucleus_target(float top_p, u64 S) {
+  u64 T = (u64)ceil((double)top_p * (double)S);
+  if (T < 1) T = 1;
+  return T > S ? S : T;
+}
+
+// Whether row r has drafted children (the tail: every row has one).
+AS_DEVICE bool row_has_child(const acespec::VocabArgs &a, size_t srow0, int r) {
+  if (a.tail) return true;
+  bool any = false;
+  for (int c = r + 1; c < a.n1; ++c) any |= a.par[srow0 + c] == r;
+  return any;
+}
+
+// The row's maximum from the LM head's column tiles (+inf when a logit is not finite).
+AS_DEVICE float tile_row_max(const acespec::VocabArgs &a, int row, VScan &sm) {
+  const float *tm = a.tile_max + (size_t)row * a.ntile;
+  float mx = -INFINITY;
+  for (int t = threadIdx.x; t < a.ntile; t += VT) mx = max_or_inf(mx, tm[t]);
+  return block_max(mx, sm);
+}
+
+// ------------------------------------------------------------------------------------
+// Few rows: one workgroup a row leaves most CUs idle and is a chain of latencies over the
+// whole row (17 rows of 128256 ids: 150 us).  The passes are split over `chunks` workgroups
+// a row, a kernel each, with the same integer sums and the same exact thresholds, so the
+// results are those of the whole-row kernel, bit for bit:
+//   hist     each chunk's histogram over 1024 bins of the exponent (M - z) log2(e) / T, 0.04
+//            wide (finer where it matters than the key's top bits, and evenly filled)
+//   bins     one workgroup a row: sums the chunks' histograms, finds the bins in which the
+//            top-p mass and the k-th id fall
+//   collect  keys and ids of those two bins' elements (a few hundred)
+//   select   one workgroup a row: exact thresholds from that list
+//   segments each chunk's part of pass 4
+//   finish   vocab_verify_kernel<true>, from the prefix sums on
+// A row whose list overflows, or with more than TIES ids tied at a threshold, is marked and
+// done whole by the last kernel.
+// ------------------------------------------------------------------------------------
+constexpr int NBIN = 1024;
+constexpr float BIN_PER = 25.f;     // bins per unit of the base-2 exponent
+constexpr int LCAP = 4096;          // listed elements a row
+constexpr int TIES = 16;
+struct RowState {
+  uint32_t nlist, ntop, whole, badq;   // whole: the last kernel does the row by itself
+  int bp, bk;
+  u64 T_p, ap, ak;
+  Sel sel;
+  uint32_t nan;
+  int32_t tie_p[TIES], tie_k[TIES];    // ids tied at the thresholds (when more than one)
+  uint32_t top_key[KMAX];
+  int32_t top_id[KMAX];
+  uint32_t top_in[KMAX];
+};
+
+// Monotone in z (each step is): larger logits, larger bins.
+AS_DEVICE int exp_bin(float z, float M, float c_hi) {
+  const float t = (z - M) * c_hi * -BIN_PER;
+  return NBIN - 1 - (int)fminf(t, (float)(NBIN - 1));
+}
+
+struct SplitView {   // one row's part of the scratch
+  RowState *st;
+  uint32_t *cnt;     // [chunks][NBIN]
+  u64 *mass;         // [chunks][NBIN]
+  uint2 *list;       // [LCAP] key, id
+  u64 *seg_p, *seg_r;
+};
+__host__ __device__ constexpr size_t split_row_bytes(int chunks, int nseg) {
+  return ((sizeof(RowState) + 255) & ~(size_t)255) + (size_t)chunks * NBIN * 12 +
+         (size_t)LCAP * 8 + (((size_t)nseg * 16 + 255) & ~(size_t)255);
+}
+AS_DEVICE SplitView split_view(const acespec::VocabArgs &a, int row) {
+  const int nseg = (a.V + SEG - 1) / SEG;
+  char *p = (char *)a.split + (size_t)row * split_row_bytes(a.chunks, nseg);
+  SplitView v;
+  v.st = (RowState *)p;
+  p += (sizeof(RowState) + 255) & ~(size_t)255;
+  v.mass = (u64 *)p;
+  p += (size_t)a.chunks * NBIN * 8;
+  v.cnt = (uint32_t *)p;
+  p += (size_t)a.chunks * NBIN * 4;
+  v.list = (uint2 *)p;
+  p += (size_t)LCAP * 8;
+  v.seg_p = (u64 *)p;
+  v.seg_r = v.seg_p + nseg;
+  return v;
+}
+// Segments of chunk c.
+AS_DEVICE void chunk_range(const acespec::VocabArgs &a, int c, int &sb, int &se) {
+  const int nseg = (a.V + SEG - 1) / SEG;
+  sb = (int)((long long)nseg * c / a.chunks);
+  se = (int)((long long)nseg * (c + 1) / a.chunks);
+}
+
+__global__ __launch_bounds__(VT) void vocab_hist_kernel(acespec::VocabArgs a) {
+  __shared__ VScan sm;
+  __shared__ uint32_t cnt[NBIN];
+  __shared__ u64 mass[NBIN];
+  const int row = blockIdx.x / a.chunks, c = blockIdx.x - row * a.chunks, tid = threadIdx.x;
+  const SplitView v = split_view(a, row);
+  Sel sel;
+  sel.M = tile_row_max(a, row, sm);
+  sel.c_hi = a.c_hi;
+  sel.c_lo = a.c_lo;
+  if (c == 0 && tid == 0) {
+    v.st->nlist = v.st->ntop = v.st->badq = 0;
+    v.st->whole = v.st->nan = !(sel.M <= 3.402823466e38f);
+    v.st->sel.M = sel.M;
+  }
+  if (!(sel.M <= 3.402823466e38f)) return;
+  for (int i = tid; i < NBIN; i += VT) {
+    cnt[i] = 0;
+    mass[i] = 0;
+  }
+  __syncthreads();
+  int sb, se;
+  chunk_range(a, c, sb, se);
+  const int i_end = min(se * SEG, a.V);
+  const float *z = a.logits + (size_t)row * a.V;
+  for (RowStream rs(z, i_end, sb * SEG + tid * 4); rs.more(); rs.advance()) {
+    rs.prefetch();
+#pragma unroll
+    for (int u = 0; u < VR; ++u) {
+      if (rs.i0 + u * VT * 4 >= i_end) break;
+      const float zz[4] = {rs.cur[u].x, rs.cur[u].y, rs.cur[u].z, rs.cur[u].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int b = exp_bin(zz[j], sel.M, sel.c_hi);
+        atomicAdd(&cnt[b], 1u);
+        atomicAdd(&mass[b], fixw(elem_e(zz[j], sel)));
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < NBIN; i += VT) {
+    v.cnt[(size_t)c * NBIN + i] = cnt[i];
+    v.mass[(size_t)c * NBIN + i] = mass[i];
+  }
+}
+
+__global__ __launch_bounds__(VT) void vocab_bins_kernel(acespec::VocabArgs a) {
+  __shared__ VScan sm;
+  __shared__ uint32_t cnt[NBIN];
+  __shared__ u64 mass[NBIN];
+  const int row = blockIdx.x, tid = threadIdx.x;
+  const SplitView v = split_view(a, row);
+  if (v.st->nan) return;
+  u64 tot = 0;
+  for (int i = tid; i < NBIN; i += VT) {
+    uint32_t n = 0;
+    u64 m = 0;
+#pragma unroll 8
+    for (int c = 0; c < a.chunks; ++c) {
+      n += v.cnt[(size_t)c * NBIN + i];
+      m += v.mass[(size_t)c * NBIN + i];
+    }
+    cnt[i] = n;
+    mass[i] = m;
+    tot += m;
+  }
+  const u64 T_p = nucleus_target(a.top_p, block_sum(tot, sm));
+  int bp, bk;
+  u64 ap, ak;
+  select_bin<true>(sm, cnt, mass, NBIN, T_p, 0, bp, ap);
+  select_bin<false>(sm, cnt, mass, NBIN, (u64)a.k, 0, bk, ak);
+  if (tid == 0) {
+    v.st->bp = bp;
+    v.st->bk = bk;
+    v.st->T_p = T_p;
+    v.st->ap = ap;
+    v.st->ak = ak;
+  }
+}
+
+__global__ __launch_bounds__(VT) void vocab_collect_kernel(acespec::VocabArgs a) {
+  __shared__ uint2 list[LCAP / 2];
+  __shared__ uint32_t n, at;
+  const int row = blockIdx.x / a.chunks, c = blockIdx.x - row * a.chunks, tid = threadIdx.x;
+  const SplitView v = split_view(a, row);
+  if (v.st->nan) return;
+  const int bp = v.st->bp, bk = v.st->bk;
+  const float M = v.st->sel.M;
+  if (tid == 0) n = 0;
+  __syncthreads();
+  int sb, se;
+  chunk_range(a, c, sb, se);
+  const int i_end = min(se * SEG, a.V);
+  const float *z = a.logits + (size_t)row * a.V;
+  for (RowStream rs(z, i_end, sb * SEG + tid * 4); rs.more(); rs.advance()) {
+    rs.prefetch();
+#pragma unroll
+    for (int u = 0; u < VR; ++u) {
+      if (rs.i0 + u * VT * 4 >= i_end) break;
+      const float zz[4] = {rs.cur[u].x, rs.cur[u].y, rs.cur[u].z, rs.cur[u].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int b = exp_bin(zz[j], M, a.c_hi);
+        if (b == bp || b == bk) {
+          const uint32_t slot = atomicAdd(&n, 1u);
+          if (slot < LCAP / 2) list[slot] = make_uint2(f32_key(zz[j]), rs.i0 + u * VT * 4 + j);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (n == 0) return;
+  // past LCAP (or more than fit here): the row is done whole
+  if (tid == 0) at = atomicAdd(&v.st->nlist, n <= LCAP / 2 ? n : LCAP + 1);
+  __syncthreads();
+  for (uint32_t i = tid; i < min(n, LCAP / 2u) && at + i < LCAP; i += VT) v.list[at + i] = list[i];
+}
+
+__global__ __launch_bounds__(VT) void vocab_select_kernel(acespec::VocabArgs a) {
+  __shared__ VSmem sm;
+  __shared__ uint32_t keys[LCAP];
+  __shared__ uint32_t lo_p, hi_p, lo_k, hi_k, np, nk;
+  const int row = blockIdx.x, tid = threadIdx.x;
+  const SplitView v = split_view(a, row);
+  RowState &st = *v.st;
+  if (st.nan) return;
+  const uint32_t n = st.nlist;
+  if (n > LCAP) {
+    if (tid == 0) st.whole = 1;
+    return;
+  }
+  Sel sel;
+  sel.M = st.sel.M;
+  sel.c_hi = a.c_hi;
+  sel.c_lo = a.c_lo;
+  const int bp = st.bp, bk = st.bk;
+  const u64 T_p = st.T_p;
+  if (tid == 0) {
+    lo_p = lo_k = ~0u;
+    hi_p = hi_k = 0;
+    np = nk = 0;
+  }
+  __syncthreads();
+  uint32_t mn_p = ~0u, mx_p = 0, mn_k = ~0u, mx_k = 0;
+  for (uint32_t i = tid; i < n; i += VT) {
+    const uint32_t key = v.list[i].x;
+    keys[i] = key;
+    const int b = exp_bin(key_to_f32(key), sel.M, sel.c_hi);
+    if (b == bp) { mn_p = min(mn_p, key); mx_p = max(mx_p, key); }
+    if (b == bk) { mn_k = min(mn_k, key); mx_k = max(mx_k, key); }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    mn_p = min(mn_p, (uint32_t)__shfl_xor((int)mn_p, o));
+    mx_p = max(mx_p, (uint32_t)__shfl_xor((int)mx_p, o));
+    mn_k = min(mn_k, (uint32_t)__shfl_xor((int)mn_k, o));
+    mx_k = max(mx_k, (uint32_t)__shfl_xor((int)mx_k, o));
+  }
+  if ((tid & 63) == 0) {
+    atomicMin(&lo_p, mn_p);
+    atomicMax(&hi_p, mx_p);
+    atomicMin(&lo_k, mn_k);
+    atomicMax(&hi_k, mx_k);
+  }
+  __syncthreads();
+  // radix steps over key - lo, 11 bits at a time from the top of the bins' key ranges
+  uint32_t bp_lo = lo_p, bk_lo = lo_k, w_p = hi_p - lo_p, w_k = hi_k - lo_k;  // width - 1
+  u64 above_p = st.ap, above_k = st.ak;
+  while (true) {
+    const uint32_t w = max(w_p, w_k);
+    const int bits = 32 - (w ? __clz((int)w) : 32), sh = bits > 11 ? bits - 11 : 0;
+    __syncthreads();
+    for (int i = tid; i < 2048; i += VT) {
+      sm.r.cnt[i] = 0;
+      sm.r.mass[i] = 0;
+      sm.r.cntk[i] = 0;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += VT) {
+      const uint32_t key = keys[i], dp = key - bp_lo, dk = key - bk_lo;
+      if (key >= bp_lo && dp <= w_p) {
+        atomicAdd(&sm.r.cnt[dp >> sh], 1u);
+        atomicAdd(&sm.r.mass[dp >> sh], fixw(elem_e(key_to_f32(key), sel)));
+      }
+      if (key >= bk_lo && dk <= w_k) atomicAdd(&sm.r.cntk[dk >> sh], 1u);
+    }
+    __syncthreads();
+    int sp, sk;
+    u64 ap2, ak2;
+    select_bin<true>(sm, sm.r.cnt, sm.r.mass, 2048, T_p, above_p, sp, ap2);
+    select_bin<false>(sm, sm.r.cntk, sm.r.mass, 2048, (u64)a.k, above_k, sk, ak2);
+    above_p = ap2;
+    above_k = ak2;
+    bp_lo += (uint32_t)sp << sh;
+    bk_lo += (uint32_t)sk << sh;
+    if (sh == 0) {
+      sel.tau_p = bp_lo;
+      sel.tau_k = bk_lo;
+      sel.c_p = sm.r.cnt[sp];
+      sel.c_k = sm.r.cntk[sk];
+      const u64 w_tau = sm.r.mass[sp] / (sel.c_p ? sel.c_p : 1);
+      const u64 need = T_p - above_p;  // > 0
+      u64 j = w_tau ? (need + w_tau - 1) / w_tau : 1;
+      if (j < 1) j = 1;
+      if (j > sel.c_p) j = sel.c_p;
+      sel.above_p = above_p;
+      sel.above_k = (uint32_t)above_k;
+      sel.j_p = (uint32_t)j;
+      sel.j_k = (uint32_t)((u64)a.k - above_k);
+      const double inv = 1.0 / (double)(above_p + j * w_tau);
+      sel.inv_hi = (float)inv;
+      sel.inv_lo = (float)(inv - (double)sel.inv_hi);
+      break;
+    }
+    w_p = w_k = (1u << sh) - 1;
+  }
+  const bool many = sel.c_p > TIES || sel.c_k > TIES;
+  if (tid == 0) {
+    st.sel = sel;
+    if (many) st.whole = 1;
+  }
+  if (many) return;
+  for (uint32_t i = tid; i < n; i += VT) {
+    const uint2 e = v.list[i];
+    if (sel.c_p > 1 && e.x == sel.tau_p) st.tie_p[atomicAdd(&np, 1u)] = (int32_t)e.y;
+    if (sel.c_k > 1 && e.x == sel.tau_k) st.tie_k[atomicAdd(&nk, 1u)] = (int32_t)e.y;
+  }
+}
+
+// Ids of a tie list before segment s.
+AS_DEVICE uint32_t ties_before(const int32_t *ids, uint32_t n, int s) {
+  uint32_t r = 0;
+  for (uint32_t i = 0; i < n; ++i) r += ids[i] < s * SEG;
+  return r;
+}
+
+__global__ __launch_bounds__(VT, 8) void vocab_segments_kernel(acespec::VocabArgs a) {
+  __shared__ VTop sm;
+  __shared__ uint32_t at;
+  const int row = blockIdx.x / a.chunks, c = blockIdx.x - row * a.chunks, tid = threadIdx.x;
+  const SplitView v = split_view(a, row);
+  RowState &st = *v.st;
+  if (st.whole) return;
+  const Sel sel = st.sel;
+  if (tid == 0) sm.ncand = 0;
+  __syncthreads();
+  const int b = row / a.n1;
+  const bool resid = !a.q_scalar && row_has_child(a, (size_t)b * a.n1, row - b * a.n1);
+  int sb, se;
+  chunk_range(a, c, sb, se);
+  const bool badq = segment_pass(
+      a.logits + (size_t)row * a.V, resid ? a.q + (size_t)row * a.V : nullptr, a.V, sb, se, resid,
+      sel, sm,
+      [&](int s, uint32_t &tp, uint32_t &tk) {
+        tp = sel.c_p > 1 ? ties_before(st.tie_p, sel.c_p, s) : 0;
+        tk = sel.c_k > 1 ? ties_before(st.tie_k, sel.c_k, s) : 0;
+      },
+      v.seg_p, v.seg_r);
+  if (badq) st.badq = 1;
+  __syncthreads();
+  const uint32_t n = min(sm.ncand, (uint32_t)KMAX);
+  if (n == 0) return;
+  if (tid == 0) at = atomicAdd(&st.ntop, n);
+  __syncthreads();
+  if (tid < (int)n && at + tid < (uint32_t)KMAX) {
+    st.top_key[at + tid] = sm.cand_key[tid];
+    st.top_id[at + tid] = sm.cand_id[tid];
+    st.top_in[at + tid] = sm.cand_in[tid];
+  }
+}
+
 // (six waves a SIMD: three 8-wave rows per CU, which caps the kernel at 80 VGPRs)
+// SPLIT: the row's thresholds, segment masses and top-k ids come from the kernels above.
+template <bool SPLIT>
 __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs a) {
   __shared__ VSmem sm;
   const int row = blockIdx.x;
@@ -343,7 +792,9 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
   // ---- pass 0: row max (+inf when a logit is not finite) -------------------------------
   float mx = -INFINITY;
   if (tid == 0) sm.flag = 0;
-  if (a.tile_max) {  // the LM head's epilogue left the row's maximum per column tile
+  if (SPLIT) {
+    mx = split_view(a, row).st->sel.M;
+  } else if (a.tile_max) {  // the LM head's epilogue left the row's maximum per column tile
     const float *tm = a.tile_max + (size_t)row * a.ntile;
     for (int t = tid; t < a.ntile; t += VT) mx = max_or_inf(mx, tm[t]);
   } else {
@@ -389,6 +840,23 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
     return;
   }
 
+  if (SPLIT && !split_view(a, row).st->whole) {
+    const SplitView v = split_view(a, row);
+    const RowState &st = *v.st;
+    sel = st.sel;
+    for (int s = tid; s < nseg; s += VT) {
+      sm.g.seg_p[s] = v.seg_p[s];
+      sm.g.seg_r[s] = v.seg_r[s];
+      if (sel.c_p > 1) sm.g.tie_p[s] = ties_before(st.tie_p, sel.c_p, s);
+    }
+    if (tid < a.k) {
+      sm.cand_key[tid] = st.top_key[tid];
+      sm.cand_id[tid] = st.top_id[tid];
+      sm.cand_in[tid] = st.top_in[tid];
+    }
+    if (tid == 0 && st.badq) sm.flag = ACESPEC_EBADDRAFT;
+    __syncthreads();
+  } else {
   // ---- pass 1: total mass, 12-bit histograms ---------------------------------------
   for (int i = tid; i < 4096; i += VT) {
     sm.h.cnt[i] = 0;
@@ -416,10 +884,7 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
     }
   }
   const u64 S_fx = block_sum(tot, sm);  // includes a barrier after the histogram writes
-  double tp = ceil((double)a.top_p * (double)S_fx);
-  u64 T_p = (u64)tp;
-  if (T_p < 1) T_p = 1;
-  if (T_p > S_fx) T_p = S_fx;
+  const u64 T_p = nucleus_target(a.top_p, S_fx);
   const u64 K = (u64)a.k;
 
   int bp, bk;
@@ -573,82 +1038,19 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
   }
 
   // ---- pass 4: id-ordered segments: masses of p_r and of the residual, top-k ids ----------
-  bool has_child = tail;
-  if (!tail) {
-    for (int c = r + 1; c < a.n1; ++c) has_child |= a.par[srow0 + c] == r;
+  const bool resid = !a.q_scalar && row_has_child(a, srow0, r);
+  const bool badq = segment_pass(
+      z, resid ? a.q + (size_t)row * V : nullptr, V, 0, nseg, resid, sel, sm,
+      [&](int sg, uint32_t &tp, uint32_t &tk) { tp = sm.g.tie_p[sg]; tk = sm.g.tie_k[sg]; },
+      sm.g.seg_p, sm.g.seg_r);
+  if (__syncthreads_or(badq) && tid == 0) sm.flag = ACESPEC_EBADDRAFT;
   }
+  const bool has_child = row_has_child(a, srow0, r);
   // Scalar mode: the uplink carries only q-hat of each drafted token (one float per
   // child row); the cloud then tests acceptance and does no sampling, so the residual
   // mass (the only reader of a dense q row) is not needed.
   const bool dense_q = a.q_scalar == nullptr;
-  const bool resid = has_child && dense_q;
   const float *q = dense_q ? a.q + (size_t)row * V : nullptr;
-  // The VU segments of a step are loaded before any is used.  Past the end of the row the
-  // last float4 is loaded again (unconditional loads); those lanes are not valid below.
-  // Every draft probability read is checked: NaN, infinite or negative flags the row.
-  bool badq = false;
-  for (int s0 = wave; s0 < nseg; s0 += NWV * VU) {
-  float4 z4u[VU], q4u[VU];
-#pragma unroll
-  for (int u = 0; u < VU; ++u) {
-    const int id0 = (s0 + u * NWV) * SEG + lane * 4;
-    const int ld = id0 < V ? id0 : V - 4;
-    // last pass over the row and its draft q: streamed past L2 and the MALL (the
-    // earlier passes keep the default policy, so their re-reads may hit the MALL)
-    z4u[u] = ld_stream(z + ld);
-    q4u[u] = resid ? ld_stream(q + ld) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int u = 0; u < VU; ++u) {
-    const int s = s0 + u * NWV;
-    if (s >= nseg) break;
-    const int id0 = s * SEG + lane * 4;
-    const bool valid = id0 < V;
-    const float4 z4 = z4u[u], q4 = q4u[u];
-    const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
-    const float qq[4] = {q4.x, q4.y, q4.z, q4.w};
-    uint32_t key[4], rp[4], rk[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) key[j] = f32_key(zz[j]);
-    if (sel.c_p > 1) tie_ranks(key, valid, sel.tau_p, sm.g.tie_p[s], rp);
-    else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rp[j] = 0;
-    }
-    if (sel.c_k > 1) tie_ranks(key, valid, sel.tau_k, sm.g.tie_k[s], rk);
-    else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rk[j] = 0;
-    }
-    u64 sp_ = 0, sr_ = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (!valid) continue;
-      const bool inn = in_nucleus(key[j], rp[j], sel);
-      const float p = elem_p(zz[j], inn, sel);
-      sp_ += fixw(p);
-      if (resid) {
-        badq |= !(qq[j] >= 0.f && qq[j] <= 3.402823466e38f);
-        sr_ += fixw(fmaxf(p - qq[j], 0.f));
-      }
-      if (in_topk(key[j], rk[j], sel)) {
-        const uint32_t slot = atomicAdd(&sm.ncand, 1u);
-        if (slot < KMAX) {
-          sm.cand_key[slot] = key[j];
-          sm.cand_id[slot] = id0 + j;
-          sm.cand_in[slot] = inn ? 1u : 0u;
-        }
-      }
-    }
-    sp_ = wave_sum_u64(sp_);
-    sr_ = wave_sum_u64(sr_);
-    if (lane == 0) {
-      sm.g.seg_p[s] = sp_;
-      sm.g.seg_r[s] = sr_;
-    }
-  }
-  }
-  if (__syncthreads_or(badq) && tid == 0) sm.flag = ACESPEC_EBADDRAFT;
   // exclusive prefixes over segments
   u64 Ptot, Rtot;
   {
@@ -780,9 +1182,38 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
 
 namespace acespec {
 
-hipError_t launch_vocab(const VocabArgs &a, hipStream_t s) {
-  if (a.V > SEGMAX * SEG || a.k > KMAX || a.k < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(vocab_verify_kernel, dim3(a.rows), dim3(VT), 0, s, a);
+// Chunks of a row, 1: whole rows.  Six launches take about 45 us however small they are, a
+// whole row of 32000 ids 60, of 128256 ids 170, as long as each row has a CU to itself; the
+// rows' bytes take over from there (split against whole, us: 128256 ids, 16 rows 51 / 172,
+// 128 95 / 175, 512 253 / 297; 32000 ids, 128 rows 55 / 62, 200 rows 64 / 62).
+int vocab_chunks(int rows, int V, bool have_max) {
+  if (!have_max || rows < 1 || V < 16384 || rows > (V >= 48000 ? kVocabSplitRows : 128)) return 1;
+  const int nseg = (V + SEG - 1) / SEG;
+  int c = 1024 / rows;   // every CU holds four of the chunks' workgroups
+  if (c > 32) c = 32;
+  if (c > nseg / 8) c = nseg / 8;
+  return c < 1 ? 1 : c;
+}
+size_t vocab_split_bytes(int rows, int V) {
+  const int c = vocab_chunks(rows, V, true);
+  return c > 1 ? (size_t)rows * split_row_bytes(c, (V + SEG - 1) / SEG) : 0;
+}
+
+hipError_t launch_vocab(const VocabArgs &args, hipStream_t s) {
+  if (args.V > SEGMAX * SEG || args.k > KMAX || args.k < 1) return hipErrorInvalidValue;
+  VocabArgs a = args;
+  a.chunks = vocab_chunks(a.rows, a.V, a.tile_max != nullptr);
+  const dim3 rows(a.rows), parts(a.rows * a.chunks), block(VT);
+  if (a.chunks == 1 || !a.split || vocab_split_bytes(a.rows, a.V) > a.split_bytes) {
+    hipLaunchKernelGGL(vocab_verify_kernel<false>, rows, block, 0, s, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(vocab_hist_kernel, parts, block, 0, s, a);
+  hipLaunchKernelGGL(vocab_bins_kernel, rows, block, 0, s, a);
+  hipLaunchKernelGGL(vocab_collect_kernel, parts, block, 0, s, a);
+  hipLaunchKernelGGL(vocab_select_kernel, rows, block, 0, s, a);
+  hipLaunchKernelGGL(vocab_segments_kernel, parts, block, 0, s, a);
+  hipLaunchKernelGGL(vocab_verify_kernel<true>, rows, block, 0, s, a);
   return hipGetLastError();
 }
 

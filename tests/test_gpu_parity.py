@@ -297,6 +297,25 @@ def test_tail_exact_logit_ties(packed):
     _run_tail(w, W=W, packed=packed)
 
 
+@pytest.mark.parametrize("rows, V, kind", [
+    (1, 16384, "plain"), (32, 20000, "plain"), (128, 16640, "plain"), (129, 16384, "plain"),
+    (40, 50004, "plain"), (512, 48000, "plain"), (513, 48000, "plain"),
+    (32, 20000, "ties8"), (32, 20000, "ties24"), (32, 20000, "flat"), (32, 20000, "cold")])
+def test_tail_split_rows(rows, V, kind):
+    """Few rows of a large vocabulary are verified by several workgroups a row: at the edges
+    of that rule, with ids tied at the thresholds (few: their ranks come from a list; many:
+    the row is done whole), a nearly uniform target (the list overflows) and a near-greedy target
+    (all but a few ids without mass)."""
+    w = synth.get("8b-lmhead-tail").scaled(name="tail-split", d=128, V=V, rows=rows, chain_len=1,
+                                          top_k=40, T={"cold": 0.03, "flat": 40.0}.get(kind, 0.8),
+                                          top_p=0.6)
+    W = synth.make_weights(w, "cuda")
+    if kind.startswith("ties"):
+        n = int(kind[4:])
+        W.lm_head = W.lm_head[torch.arange(w.V, device="cuda") // n].contiguous()
+    _run_tail(w, W=W)
+
+
 @pytest.mark.parametrize("T,top_p,top_k", [
     (1.0, 1.0, 256),    # whole vocabulary in the nucleus, the largest payload
     (0.05, 0.9, 1),     # near-greedy target, a one-token payload

@@ -145,3 +145,32 @@ def test_tail_hidden_overflow_flags_only_its_chain():
     normed = tail(hidden, final_norm=torch.ones(w.d, dtype=torch.bfloat16, device="cuda"))
     assert normed["status"].tolist() == [0] * nch
     v.close()
+
+
+def test_split_rows_flag_only_their_chain():
+    """The same, and a bad draft distribution, where a row's vocabulary is split over several
+    workgroups (a large vocabulary, few rows)."""
+    w = synth.get("8b-lmhead-tail").scaled(name="tail-ovf-split", d=256, V=20000, rows=24,
+                                          chain_len=8, top_k=16)
+    W = synth.make_weights(w, "cuda")
+    batch = synth.make_batch(w, "cuda", weights=W)
+    v = A.Verifier.for_workload(w)
+
+    def tail(hidden, q):
+        outs = v.alloc_outputs(w.rows, 3, w.chain_len, w.top_k, w.V, "cuda", True)
+        v.verify_tail(W.lm_head, None, hidden, batch.draft_tokens, q, batch.u, w.chain_len, w.T,
+                      w.top_p, w.top_k, outs)
+        torch.cuda.synchronize()
+        return {k: (t.cpu() if t is not None else None) for k, t in outs.items()}
+
+    clean = tail(batch.hidden, batch.q)
+    assert clean["status"].tolist() == [0, 0, 0]
+    hidden, q = batch.hidden.clone(), batch.q.clone()
+    hidden[3, 10] = 1.0e5
+    q[20, 19999] = float("nan")
+    bad = tail(hidden, q)
+    assert bad["status"].tolist() == [A.ACESPEC_ENONFINITE, 0, A.ACESPEC_EBADDRAFT]
+    assert (bad["topk_ids"][3] == -1).all() and bad["bonus_token"][3] == -1
+    for k in ("accept", "resample_token", "bonus_token", "topk_ids", "logits_out"):
+        assert torch.equal(clean[k][8:16], bad[k][8:16]), k
+    v.close()
