@@ -141,3 +141,66 @@ def test_convert_v_cache_is_an_exact_transpose_both_ways(dtype):
         want = slot_major.transpose(1, 2).contiguous()
         assert torch.equal(hd_major.view(iview), want.view(iview))
         assert torch.equal(back.view(iview), slot_major.view(iview))
+
+
+@pytest.mark.parametrize("dtype, hd, N, shift", [
+    ("bf16", 64, 1, 0), ("bf16", 128, 16, 0), ("bf16", 128, 64, 0), ("f32", 128, 64, 0),
+    ("f32", 64, 7, 0), ("bf16", 64, 33, 1), ("f32", 128, 12, 1)])
+def test_commit_moves_any_kept_rows(dtype, hd, N, shift):
+    """commit_kv against a gather on the host side of torch, bit for bit: trees of 1 to 64
+    nodes, 0 .. N kept rows in any order (a destination slot may be another entry's source),
+    caches that are not 16-byte aligned (shift, in elements)."""
+    from paper_2609_02514_amd.acespec import Verifier
+    L, B, Hkv, S = 2, 9, 3, 50
+    cap = (S + N + 1 + 63) // 64 * 64
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(N * 7 + hd)
+
+    def cache(*shape):
+        n = int(np.prod(shape))
+        return torch.randn(n + shift, generator=g).to(tdt).cuda()[shift:].view(*shape)
+
+    k, v = cache(L, B, Hkv, cap, hd), cache(L, B, Hkv, hd, cap)
+    k0, v0 = k.clone(), v.clone()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    path = torch.full((B, N + 1), -1, dtype=torch.int32)
+    plen = [min(N, n) for n in (0, 1, 2, 3, 5, 8, 31, 32, N)]
+    for b, n in enumerate(plen):
+        path[b, :n] = torch.randperm(N, generator=g)[:n].int() + 1
+    ver = Verifier(L, 256, Hkv, Hkv, hd, 256, 1024, dtype, B, N)
+    new = torch.full((B,), -7, **i32)
+    hz.log(f"commit_kv {dtype} hd={hd} N={N} shift={shift}")
+    ver.commit_kv(k, v, cap, torch.full((B,), S, **i32), path.cuda(), torch.tensor(plen, **i32),
+                  torch.zeros(B, **i32), new)
+    torch.cuda.synchronize()
+    assert new.tolist() == [S + 1 + n for n in plen]
+    for b, n in enumerate(plen):
+        src = S + path[b, :n].long().cuda()
+        k0[:, b, :, S + 1:S + 1 + n] = k0[:, b, :, src].clone()
+        v0[:, b, :, :, S + 1:S + 1 + n] = v0[:, b, :, :, src].clone()
+    iview = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(k.view(iview), k0.view(iview))
+    assert torch.equal(v.view(iview), v0.view(iview))
+    ver.close()
+
+
+@pytest.mark.parametrize("dtype, hd, cap, shift", [
+    ("bf16", 8, 64, 0), ("bf16", 72, 192, 0), ("bf16", 20, 64, 0), ("f32", 20, 128, 0),
+    ("f32", 130, 64, 0), ("bf16", 64, 128, 1), ("f32", 64, 64, 1)])
+def test_convert_v_cache_pieces_and_elements(dtype, hd, cap, shift):
+    """Head dims at the edges of the 64-wide tiles, ones that are not whole 16-byte pieces and
+    arrays that are not 16-byte aligned (both take the element-wise kernel)."""
+    from paper_2609_02514_amd import acespec as A
+    tdt, idt = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
+    adt = A.ACESPEC_BF16 if dtype == "bf16" else A.ACESPEC_F32
+    n = 5 * cap * hd
+    src = torch.randn(n + shift).to(tdt).cuda()[shift:].view(5, cap, hd)
+    dst, back = (torch.empty(n + shift, dtype=tdt, device="cuda")[shift:] for _ in range(2))
+    stream = torch.cuda.current_stream().cuda_stream
+    A.acespec_convert_v_cache(src.data_ptr(), dst.data_ptr(), 5, cap, hd, adt,
+                              A.ACESPEC_V_TO_HEAD_DIM_MAJOR, stream)
+    A.acespec_convert_v_cache(dst.data_ptr(), back.data_ptr(), 5, cap, hd, adt,
+                              A.ACESPEC_V_TO_SLOT_MAJOR, stream)
+    torch.cuda.synchronize()
+    assert torch.equal(dst.view(idt).view(5, hd, cap), src.transpose(1, 2).contiguous().view(idt))
+    assert torch.equal(back.view(idt), src.reshape(-1).view(idt))
