@@ -41,7 +41,7 @@
 //  With several splits, unnormalised partial outputs and (max, sum) pairs are merged by
 //  a small combine kernel.
 //
-// fp32 kernel (tiny models): one wave per (tree row, query head), keys in sequence.
+// fp32 kernel (small models): one workgroup per (tree row, query head).
 #include "common.h"
 
 namespace {
@@ -918,36 +918,89 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
       f16x4{(f16)(num.x * inv), (f16)(num.y * inv), (f16)(num.z * inv), (f16)(num.w * inv)};
 }
 
-// fp32 path: one wave per (tree row, query head); lane i owns dims i and i + 64.
-__global__ __launch_bounds__(64) void tree_attn_f32_kernel(
+// fp32 path: one workgroup per (tree row, query head).  256 slots at a time: scores with
+// HD / 4 lanes a slot (16-byte pieces of a key row, summed by lane swaps), a softmax step
+// over the block with the usual running maximum, then the values: 16 lanes x 4 slots of a
+// head dim, whose sums stay in registers until the end.  (One wave walking the slots one by
+// one, each behind a reduction over the wave, took 62 us at 137 slots, this 10.)
+template <int HD>
+__global__ __launch_bounds__(256) void tree_attn_f32_kernel(
     const float *__restrict__ qin, const float *__restrict__ ck, const float *__restrict__ cv,
-    TreeMeta meta, float *__restrict__ out, int n1, int H, int Hkv, int HD, int capacity) {
+    TreeMeta meta, float *__restrict__ out, int n1, int H, int Hkv, int capacity) {
+  constexpr int LPS = HD / 4, SPW = 64 / LPS;   // lanes a slot, slots a wave and load
+  constexpr int NCH = 256, STEPS = NCH / 4 / SPW;
+  constexpr int DJ = HD / 16;                   // head dims a lane sums
+  __shared__ __attribute__((aligned(16))) float p[NCH];
+  __shared__ float red[8];
   const int h = blockIdx.x, row = blockIdx.y;
   const int b = row / n1;
-  const int G = H / Hkv, g = h / G, lane = threadIdx.x;
-  const int S = meta.sess_S[b];
+  const int G = H / Hkv, g = h / G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int S = meta.sess_S[b], total = S + n1;
   const uint64_t anc = meta.anc[row];
-  const float *q = qin + (size_t)row * H * HD + h * HD;
-  const float q0 = lane < HD ? q[lane] : 0.f, q1 = lane + 64 < HD ? q[lane + 64] : 0.f;
   const float *kb = ck + ((size_t)b * Hkv + g) * capacity * HD;
   const float *vb = cv + ((size_t)b * Hkv + g) * HD * capacity;   // [HD][capacity]
+  const float4 q4 = *(const float4 *)(qin + (size_t)row * H * HD + h * HD + lane % LPS * 4);
   const float scale = 1.0f / sqrtf((float)HD);
-  float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int slot = 0; slot < S + n1; ++slot) {
-    if (!tree_visible(slot, S, n1, anc)) continue;
-    const float *k = kb + (size_t)slot * HD;
-    float part = (lane < HD ? q0 * k[lane] : 0.f) + (lane + 64 < HD ? q1 * k[lane + 64] : 0.f);
-    const float s = wave_sum(part) * scale;
-    const float mn = fmaxf(m, s);
-    const float a = expf(m - mn), p = expf(s - mn);
-    l = l * a + p;
-    o0 = o0 * a + p * (lane < HD ? vb[(size_t)lane * capacity + slot] : 0.f);
-    o1 = o1 * a + p * (lane + 64 < HD ? vb[(size_t)(lane + 64) * capacity + slot] : 0.f);
+  float m = -INFINITY, l = 0.f, o[DJ];
+#pragma unroll
+  for (int j = 0; j < DJ; ++j) o[j] = 0.f;
+  for (int c0 = 0; c0 < total; c0 += NCH) {
+    // scores of slots c0 + wave * 64 + i * SPW + lane / LPS
+    float4 kv[STEPS];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      const int slot = c0 + wave * 64 + i * SPW + lane / LPS;
+      kv[i] = *(const float4 *)(kb + (size_t)min(slot, total - 1) * HD + lane % LPS * 4);
+    }
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      const int ls = wave * 64 + i * SPW + lane / LPS, slot = c0 + ls;
+      float d = q4.x * kv[i].x + q4.y * kv[i].y + q4.z * kv[i].z + q4.w * kv[i].w;
+#pragma unroll
+      for (int x = 1; x < LPS; x <<= 1) d += __shfl_xor(d, x);
+      if (lane % LPS == 0) p[ls] = tree_visible(slot, S, n1, anc) ? d * scale : -INFINITY;
+    }
+    __syncthreads();
+    const float s = p[tid];
+    float mx = wave_max(s);
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const float mn = fmaxf(m, mx);      // finite from the first block on: the root is visible,
+    const float mu = mn == -INFINITY ? 0.f : mn;   // and prefix slots are
+    const bool vis = tree_visible(c0 + tid, S, n1, anc);
+    const float e = vis ? expf(s - mu) : 0.f, a = expf(m - mu);
     m = mn;
+    p[tid] = vis ? e : -1.f;            // (a hidden slot's value is left out, not times 0)
+    const float ls = wave_sum(e);
+    if (lane == 0) red[4 + wave] = ls;
+    __syncthreads();
+    l = l * a + ((red[4] + red[5]) + (red[6] + red[7]));
+#pragma unroll
+    for (int j = 0; j < DJ; ++j) o[j] *= a;
+    // values: lane % 16 takes slots 4 (lane % 16) + 64 i, for head dims wave * 4 + lane / 16
+    // + 16 j (the capacity is a multiple of 64: reads past the last slot stay in the row)
+    for (int i = 0; i < NCH / 64 && c0 + i * 64 < total; ++i) {
+      const int ls4 = i * 64 + lane % 16 * 4, slot = c0 + ls4;
+      const float4 w = *(const float4 *)(p + ls4);
+#pragma unroll
+      for (int j = 0; j < DJ; ++j) {
+        const float4 v = *(const float4 *)(vb + (size_t)(wave * 4 + lane / 16 + 16 * j) * capacity + slot);
+        if (w.x >= 0.f) o[j] += w.x * v.x;
+        if (w.y >= 0.f) o[j] += w.y * v.y;
+        if (w.z >= 0.f) o[j] += w.z * v.z;
+        if (w.w >= 0.f) o[j] += w.w * v.w;
+      }
+    }
+    __syncthreads();
   }
-  float *op = out + (size_t)row * (H * HD) + h * HD;
-  if (lane < HD) op[lane] = o0 / l;
-  if (lane + 64 < HD) op[lane + 64] = o1 / l;
+#pragma unroll
+  for (int j = 0; j < DJ; ++j) {
+#pragma unroll
+    for (int x = 1; x < 16; x <<= 1) o[j] += __shfl_xor(o[j], x);
+    if (lane % 16 == 0)
+      out[(size_t)row * (H * HD) + h * HD + wave * 4 + lane / 16 + 16 * j] = o[j] / l;
+  }
 }
 
 // Ring depth: 4 stages of 32 KB (head_dim 128) or 16 KB (head_dim 64).
@@ -1023,8 +1076,9 @@ hipError_t launch_attention<float>(const float *q, const float *ck, const float 
                                    long long, int B, int n1, int H, int Hkv, int hd,
                                    int capacity, int, hipStream_t s, int *nsplit_used) {
   *nsplit_used = 1;
-  hipLaunchKernelGGL(tree_attn_f32_kernel, dim3(H, B * n1), dim3(64), 0, s, q, ck, cv, meta,
-                     out, n1, H, Hkv, hd, capacity);
+  auto kernel = hd == 64 ? tree_attn_f32_kernel<64> : tree_attn_f32_kernel<128>;
+  hipLaunchKernelGGL(kernel, dim3(H, B * n1), dim3(256), 0, s, q, ck, cv, meta, out, n1, H, Hkv,
+                     capacity);
   return hipGetLastError();
 }
 

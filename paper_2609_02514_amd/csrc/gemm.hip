@@ -9,7 +9,7 @@
 //   L2.  Tiles of a last, partly empty round of workgroups (or every tile, when there
 //   are fewer tiles than workgroup slots) are sliced along K; the fp32 slices are summed
 //   in a fixed order (deterministic) by a fixup kernel that also applies the epilogue.
-// fp32 model (small models only): LDS-tiled FMA kernel with the same epilogues.
+// fp32 model (small models): gemm_rows_kernel on fp32 MFMAs, with the same epilogues.
 //
 // Epilogues fuse the elementwise work that follows each product: fp32 store (LM head,
 // with per-tile row maxima for the vocabulary kernel), RoPE + q store + cache write of
@@ -17,6 +17,7 @@
 // (attention output and MLP down projections), SwiGLU (gate/up projection: each tile
 // holds matching gate and up columns).
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 
@@ -635,18 +636,25 @@ __global__ __launch_bounds__(256) void fixup_resid_norm_kernel(
 // halve the LDS reads a column costs.  NST - 1 units of weights and activations are in
 // flight, with one barrier a unit.  Packed weights go straight to registers; row-major ones
 // through LDS too, in whole 128-byte lines.
+//   The fp32 model's products run here too (TA = float, any number of rows): both operands
+// row-major through LDS, 32 k a unit, on v_mfma_f32_16x16x4_f32, twice the rate of plain
+// FMAs and a quarter of their LDS reads.
 //   out: EPI_SWIGLU writes the activation; EPI_F32_MAX the product and tmax[row][tn], the
-// row's maximum over the 128 columns; EPI_F32 fp32 sums to outf + slice * M * N.
+// row's maximum over the 128 columns; EPI_F32 fp32 sums to outf + slice * M * N; EPI_RESID
+// adds to outf (one slice).
 // ------------------------------------------------------------------------------------
 constexpr int ROWSN = 128;
-template <int EPI, int PK, int MB, int NST>
-__global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict__ A,
+template <int EPI, typename TA, int PK, int MB, int NST>
+__global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const TA *__restrict__ A,
                                                            const void *__restrict__ W, int M,
-                                                           int N, int K, f16 *__restrict__ out,
+                                                           int N, int K, TA *__restrict__ out,
                                                            float *__restrict__ outf, int mt,
                                                            int nt, int nsl,
                                                            float *__restrict__ tmax) {
   constexpr bool SW = EPI == acespec::EPI_SWIGLU;
+  constexpr bool F32 = sizeof(TA) == 4;
+  constexpr int ES = sizeof(TA);              // bytes per element of either operand
+  static_assert(!(F32 && PK), "packed weights are 16-bit");
   constexpr int WTN = 2, TBM = MB * 16;
   constexpr int A_BYTES = MB * 2048, STAGE = A_BYTES + (PK ? 0 : ROWSN * 128);
   constexpr int ABLK = MB * 2, A_DMA = (ABLK + 7) / 8;
@@ -663,10 +671,10 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
   const int u = xcd_tile(blockIdx.x, mt * nt * nsl);
   const int sl = u / (mt * nt), tile = u - sl * mt * nt, tn = tile / mt, tm = tile - tn * mt;
   const int m0 = tm * TBM;
-  const int U = K >> 6;
+  const int U = K * ES >> 7;                  // units: 128 bytes of a row
   const int u0 = (int)((long long)U * sl / nsl), u1 = (int)((long long)U * (sl + 1) / nsl);
 
-  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A, (uint32_t)((size_t)M * K * 2));
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A, (uint32_t)((size_t)M * K * ES));
   uint32_t va[A_DMA];
   int sa[A_DMA], lb[A_DMA];
 #pragma unroll
@@ -674,21 +682,29 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
     // every wave issues A_DMA loads a unit, so that one vmcnt holds for all; a surplus one
     // is out of the buffer's range: nothing is fetched, zeros land in the spare 1 KB
     const int blk = w + t * 8;
-    const int r0 = m0 + blk / 2 * 16, rl = blk < ABLK ? min(max(M - r0, 0), 16) : 0;
-    va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2
-                    : (uint32_t)M * K * 2;
-    sa[t] = rl * 128;
     lb[t] = blk * 1024;
+    if (F32) {   // row-major: 8 rows x 128 bytes a block, swizzled like the weights
+      const int lrow = blk * 8 + (lane >> 3), r = m0 + lrow;
+      va[t] = blk < ABLK && r < M
+                  ? (uint32_t)r * K * 4 + (((lane & 7) ^ ((lrow >> 1) & 7)) << 4)
+                  : (uint32_t)M * K * 4;
+      sa[t] = 128;
+    } else {
+      const int r0 = m0 + blk / 2 * 16, rl = blk < ABLK ? min(max(M - r0, 0), 16) : 0;
+      va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2
+                      : (uint32_t)M * K * 2;
+      sa[t] = rl * 128;
+    }
   }
   // Weights, as a buffer over the tile's panel (two panels for SwiGLU: gate, up).  Packed:
   // this wave's two 16-row blocks at k step kg.  Row-major: 8-row x 128-byte blocks 2 w and
   // 2 w + 1 of the tile's 128 rows; rows past N repeat the last one.
   const int c0 = SW ? tn * (ROWSN / 2) : tn * ROWSN;
   const int npan = SW ? ROWSN / 2 : ROWSN, nrows = min(npan, N - c0);
-  const char *wbase = (const char *)W + (size_t)c0 * K * 2;
-  const uint32_t wbytes = (uint32_t)nrows * K * 2;
+  const char *wbase = (const char *)W + (size_t)c0 * K * ES;
+  const uint32_t wbytes = (uint32_t)nrows * K * ES;
   const __amdgpu_buffer_rsrc_t rsw[2] = {
-      make_rsrc(wbase, wbytes), make_rsrc(wbase + (SW ? (size_t)N * K * 2 : 0), wbytes)};
+      make_rsrc(wbase, wbytes), make_rsrc(wbase + (SW ? (size_t)N * K * ES : 0), wbytes)};
   uint32_t vw[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -697,13 +713,15 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
       vw[j] = (uint32_t)c * K * 2 + kg * 1024 + lane * 16;
     } else {
       const int row = (w * 2 + j) * 8 + (lane >> 3), r = SW ? row & 63 : row;
-      vw[j] = (uint32_t)min(r, nrows - 1) * K * 2 + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+      vw[j] = (uint32_t)min(r, nrows - 1) * K * ES + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
   }
   // (SwiGLU's panel: by the block in the packed form, by the wave in the row-major form)
   const __amdgpu_buffer_rsrc_t rsp = rsw[SW && !PK && w >= 4];
   u32x4 rb[PK ? NST : 1][WTN];
-  f16x8 fa[MB];
+  typedef typename std::conditional<F32, f32x4, f16x8>::type frag;
+  frag fa[MB];
+  const int aoff = F32 ? piece_off<128>(lr, kg * 4 + lk) : kg * 1024 + lane * 16;
   auto issue = [&](int unit, int st) {
 #pragma unroll
     for (int t = 0; t < A_DMA; ++t)
@@ -734,23 +752,34 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
   auto step = [&](int i, int s) {
     wait_vmcnt<(NST - 2) * L_VM>();
     __builtin_amdgcn_s_barrier();
-    const char *sc = smem + s * STAGE + kg * 1024 + lane * 16;
-    f16x8 b[WTN];
+    // (row block f is 2 KB further; 16 rows leave the row swizzle as it is)
+    const char *sc = smem + s * STAGE + aoff;
+    frag b[WTN];
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
       if constexpr (PK) b[j] = __builtin_bit_cast(f16x8, rb[s][j]);
+      else if constexpr (F32) b[j] = *(const f32x4 *)(smem + s * STAGE + boff[j]);
       else b[j] = bf16x8_to_f16x8(*(const bf16x8 *)(smem + s * STAGE + boff[j]));
     }
-    fa[0] = *(const f16x8 *)sc;
-    if constexpr (MB > 1) fa[1] = *(const f16x8 *)(sc + 2048);
-    if constexpr (MB > 2) fa[2] = *(const f16x8 *)(sc + 4096);
+    fa[0] = *(const frag *)sc;
+    if constexpr (MB > 1) fa[1] = *(const frag *)(sc + 2048);
+    if constexpr (MB > 2) fa[2] = *(const frag *)(sc + 4096);
 #pragma unroll
     for (int f = 0; f < MB; ++f) {
-      if (f + 3 < MB) fa[f + 3] = *(const f16x8 *)(sc + (f + 3) * 2048);
+      if (f + 3 < MB) fa[f + 3] = *(const frag *)(sc + (f + 3) * 2048);
       SCHED_FENCE();
+      if constexpr (F32) {
+        // four 4-wide steps: lane group lk holds k = 4 lk .. + 3 of both operands
 #pragma unroll
-      for (int j = 0; j < WTN; ++j)
-        acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[f], b[j], acc[f][j], 0, 0, 0);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < WTN; ++j)
+            acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[f][e], b[j][e], acc[f][j], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int j = 0; j < WTN; ++j)
+          acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[f], b[j], acc[f][j], 0, 0, 0);
+      }
       SCHED_FENCE();
       if (f == 0) issue(u0 + min(i + NST - 1, nk - 1), (s + NST - 1) % NST);
     }
@@ -794,7 +823,14 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
         if (row >= M) continue;
         if constexpr (SW) {
           const int col = tn * (ROWSN / 2) + wn * 16 + lr;
-          if (col < N) out[act_off(row, col, M, N)] = (f16)silu_mul(v[0], v[1]);
+          if (col < N)
+            out[F32 ? (size_t)row * N + col : act_off(row, col, M, N)] = (TA)silu_mul(v[0], v[1]);
+        } else if constexpr (EPI == acespec::EPI_RESID) {
+#pragma unroll
+          for (int j = 0; j < WTN; ++j) {
+            const int col = tn * ROWSN + wn * 32 + j * 16 + lr;
+            if (col < N) outf[(size_t)row * N + col] += v[j];
+          }
         } else {
 #pragma unroll
           for (int j = 0; j < WTN; ++j) {
@@ -842,7 +878,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const f16 *__restrict
 template <typename TG, int J>
 __global__ __launch_bounds__(1024) void rows_resid_norm_kernel(
     const float *__restrict__ part, float *__restrict__ x, const TG *__restrict__ gain,
-    f16 *__restrict__ out, int N, int nsl, float eps) {
+    typename ActOf<TG>::type *__restrict__ out, int N, int nsl, float eps) {
   const int M = gridDim.x, row = xcd_tile(blockIdx.x, M), tid = threadIdx.x, T = blockDim.x;
   const int n4 = N >> 2;
   const size_t slice = (size_t)M * N;
@@ -881,83 +917,11 @@ __global__ __launch_bounds__(1024) void rows_resid_norm_kernel(
     if (c >= n4) break;
     typedef TG g4 __attribute__((ext_vector_type(4)));
     const g4 g = *(const g4 *)(gain + 4 * c);
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    *(h4 *)(out + act_off(row, 4 * c, M, N)) =
-        h4{(f16)(v[j].x * scale * (float)g[0]), (f16)(v[j].y * scale * (float)g[1]),
-           (f16)(v[j].z * scale * (float)g[2]), (f16)(v[j].w * scale * (float)g[3])};
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// fp32 reference-precision path (tiny models): 64 x 64 tiles, 4 x 4 outputs per thread.
-// ------------------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A,
-                                                       const float *__restrict__ W, int M,
-                                                       int N, int K, float *__restrict__ out,
-                                                       float *__restrict__ outf) {
-  constexpr int T = 64, KS = 16;
-  __shared__ float sA[KS][T + 1];
-  __shared__ float sW[KS][2 * T + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int wcols = EPI == acespec::EPI_SWIGLU ? 2 * T : T;
-  float acc[4][8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += KS) {
-    for (int idx = tid; idx < T * KS; idx += 256) {
-      const int r = idx / KS, kk = idx % KS;
-      const int m = m0 + r;
-      sA[kk][r] = (m < M && k0 + kk < K) ? A[(size_t)m * K + k0 + kk] : 0.f;
-    }
-    for (int idx = tid; idx < wcols * KS; idx += 256) {
-      const int r = idx / KS, kk = idx % KS;
-      int wr;
-      bool ok;
-      if (EPI == acespec::EPI_SWIGLU) {
-        wr = r < T ? n0 + r : N + n0 + (r - T);
-        ok = (n0 + (r % T)) < N;
-      } else {
-        wr = n0 + r;
-        ok = wr < N;
-      }
-      sW[kk][r] = (ok && k0 + kk < K) ? W[(size_t)wr * K + k0 + kk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      float a[4], w[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = sW[kk][tx * 4 + j];
-      if (EPI == acespec::EPI_SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w[4 + j] = sW[kk][T + tx * 4 + j];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= N) continue;
-      const size_t o = (size_t)row * N + col;
-      if (EPI == acespec::EPI_SWIGLU) out[o] = silu_mul(acc[i][j], acc[i][4 + j]);
-      else if (EPI == acespec::EPI_RESID) outf[o] += acc[i][j];
-      else outf[o] = acc[i][j];
-    }
+    typedef typename ActOf<TG>::type TA;
+    typedef TA a4 __attribute__((ext_vector_type(4)));
+    *(a4 *)(out + (sizeof(TA) == 4 ? (size_t)row * N + 4 * c : act_off(row, 4 * c, M, N))) =
+        a4{(TA)(v[j].x * scale * (float)g[0]), (TA)(v[j].y * scale * (float)g[1]),
+           (TA)(v[j].z * scale * (float)g[2]), (TA)(v[j].w * scale * (float)g[3])};
   }
 }
 
@@ -1124,12 +1088,13 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
 }
 
 // gemm_rows_kernel's tiling: row tiles of up to 144 rows, as few and as low as hold M, and
-// the k-slices of the fp32 products.  A slice saves k units (about 0.35 + 0.03 mb us each,
-// one workgroup a CU) and costs its fp32 sums' round trip (about 3.5 TB/s).
+// the k-slices of the fp32 results.  A slice saves k units (about 0.35 + 0.03 mb us each,
+// one workgroup a CU; with fp32 operands 0.35 + 0.25 mb) and costs its fp32 sums' round trip
+// (about 3.5 TB/s).  es: bytes per operand element.
 struct RowsPlan {
   int mb, mt, nt, nsl;
 };
-RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap) {
+RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap, int es = 2) {
   RowsPlan p;
   p.mt = (M + 143) / 144;
   const int blocks = (M + 16 * p.mt - 1) / (16 * p.mt);
@@ -1137,11 +1102,11 @@ RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap) {
   p.nt = epi == EPI_SWIGLU ? (N + ROWSN / 2 - 1) / (ROWSN / 2) : (N + ROWSN - 1) / ROWSN;
   p.nsl = 1;
   if (epi == EPI_F32) {
-    const int U = K / 64;
-    const double unit = 0.35 + 0.03 * p.mb, sums = (double)M * N * 8 / 3.5e6;
+    const int U = K * es / 128, least = es == 4 ? 2 : 4;
+    const double unit = es == 4 ? 0.35 + 0.25 * p.mb : 0.35 + 0.03 * p.mb, sums = (double)M * N * 8 / 3.5e6;
     double best = 1e30;
     for (int n = 1; n <= 8; ++n) {
-      if (n > 1 && (n * p.mt * p.nt > cus || U / n < 4 || (long long)n * M * N > cap)) break;
+      if (n > 1 && (n * p.mt * p.nt > cus || U / n < least || (long long)n * M * N > cap)) break;
       const double t = (U + n - 1) / n * unit + n * sums;
       if (t < best) { best = t; p.nsl = n; }
     }
@@ -1164,30 +1129,36 @@ bool rows_ok(int epi, int M, int N, int K, int packed) {
   return M <= kFewRows;
 }
 
-template <int EPI>
-void launch_rows(hipStream_t s, const f16 *A, const bf16 *W, int M, int N, int K, f16 *out,
+template <int EPI, typename TA, typename TW>
+void launch_rows(hipStream_t s, const TA *A, const TW *W, int M, int N, int K, TA *out,
                  float *outf, const RowsPlan &p, int packed, float *tmax = nullptr) {
-#define ROWS(MB, NST)                                                                        \
+  // two workgroups a CU where the LM head's many tiles pass through it
+  constexpr int NROW = EPI == EPI_F32_MAX ? 3 : 4;
+#define ROWS(MB)                                                                             \
   case MB:                                                                                   \
-    if (packed)                                                                              \
-      hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, MB, NST>), grid, dim3(512), 0, s, A, W, M,  \
-                         N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                          \
+    if constexpr (sizeof(TA) == 4)                                                           \
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, float, 0, MB, 4>), grid, dim3(512), 0, s, A,   \
+                         W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                    \
+    else if (packed)                                                                         \
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 1, MB, 5>), grid, dim3(512), 0, s, A, W,  \
+                         M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                       \
     else                                                                                     \
-      hipLaunchKernelGGL((gemm_rows_kernel<EPI, 0, MB, EPI == EPI_F32_MAX && MB <= 5 ? 3 : 4>), grid, dim3(512), 0, s, A, W, M,    \
-                         N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                          \
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 0, MB, MB <= 5 ? NROW : 4>), grid,        \
+                         dim3(512), 0, s, A, W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax); \
     break
   const dim3 grid(p.mt * p.nt * p.nsl);
   switch (p.mb) {
-    ROWS(1, 5); ROWS(2, 5); ROWS(3, 5); ROWS(5, 5); ROWS(7, 5); ROWS(9, 5);
+    ROWS(1); ROWS(2); ROWS(3); ROWS(5); ROWS(7); ROWS(9);
     default: break;
   }
 #undef ROWS
 }
 
-void launch_rows_resid_norm(hipStream_t s, const float *part, float *x, const bf16 *gain,
-                            f16 *out, int M, int N, int nsl, float eps) {
+template <typename TW>
+void launch_rows_resid_norm(hipStream_t s, const float *part, float *x, const TW *gain,
+                            typename ActOf<TW>::type *out, int M, int N, int nsl, float eps) {
   const int threads = N >= 4096 ? 1024 : (N / 4 + 63) / 64 * 64;   // N <= 8192
-  auto kernel = N > 4 * threads ? rows_resid_norm_kernel<bf16, 2> : rows_resid_norm_kernel<bf16, 1>;
+  auto kernel = N > 4 * threads ? rows_resid_norm_kernel<TW, 2> : rows_resid_norm_kernel<TW, 1>;
   hipLaunchKernelGGL(kernel, dim3(M), dim3(threads), 0, s, part, x, gain, out, N, nsl, eps);
 }
 
@@ -1236,7 +1207,7 @@ hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M,
   if (rows_ok(EPI_RESID, M, N, K, aux.packed) && N <= 8 * 4 * 256 &&
       (long long)M * N <= aux.part_cap) {
     const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
-    launch_rows<EPI_F32>(s, A, W, M, N, K, nullptr, aux.part, mp, aux.packed);
+    launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, aux.part, mp, aux.packed);
     launch_rows_resid_norm(s, aux.part, x, gain, out, M, N, mp.nsl, eps);
     return hipGetLastError();
   }
@@ -1298,22 +1269,14 @@ hipError_t launch_gemm<bf16, f16>(int epi, const f16 *A, const bf16 *W, int M, i
 
 template <>
 hipError_t launch_gemm<float, float>(int epi, const float *A, const float *W, int M, int N,
-                                     int K, float *out, float *outf, const GemmAux &,
+                                     int K, float *out, float *outf, const GemmAux &aux,
                                      hipStream_t s) {
-  const dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
-  switch (epi) {
-    case EPI_RESID:
-      hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, s, A, W, M, N, K, out,
-                         outf);
-      break;
-    case EPI_SWIGLU:
-      hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, s, A, W, M, N, K, out,
-                         outf);
-      break;
-    default:
-      hipLaunchKernelGGL(gemm_f32_kernel<EPI_F32>, grid, block, 0, s, A, W, M, N, K, out,
-                         outf);
-  }
+  RowsPlan p = plan_rows(EPI_RESID, M, N, K, aux.cus, 0, 4);   // (one slice)
+  if (epi == EPI_SWIGLU)
+    launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, outf,
+                            plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0, 4), 0);
+  else if (epi == EPI_RESID) launch_rows<EPI_RESID>(s, A, W, M, N, K, out, outf, p, 0);
+  else launch_rows<EPI_F32>(s, A, W, M, N, K, out, outf, p, 0);
   return hipGetLastError();
 }
 
@@ -1321,6 +1284,12 @@ template <>
 hipError_t launch_gemm_resid_norm<float, float>(const float *A, const float *W, int M, int N,
                                                 int K, float *x, const float *gain, float *out,
                                                 float eps, const GemmAux &aux, hipStream_t s) {
+  if (N <= 8192 && (long long)M * N <= aux.part_cap) {
+    const RowsPlan p = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap, 4);
+    launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, aux.part, p, 0);
+    launch_rows_resid_norm(s, aux.part, x, gain, out, M, N, p.nsl, eps);
+    return hipGetLastError();
+  }
   hipError_t e = launch_gemm<float, float>(EPI_RESID, A, W, M, N, K, nullptr, x, aux, s);
   if (e != hipSuccess) return e;
   return launch_rmsnorm<float, float>(x, gain, out, M, N, eps, s);
@@ -1337,7 +1306,7 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
   if (rows_ok(EPI_F32, M, N, K, aux.packed)) {
     const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
     float *dst = mp.nsl > 1 ? aux.part : qkv;
-    launch_rows<EPI_F32>(s, A, W, M, N, K, nullptr, dst, mp, aux.packed);
+    launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, dst, mp, aux.packed);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_rope_kv<bf16>(dst, mp.nsl, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv,
@@ -1381,10 +1350,13 @@ hipError_t launch_qkv_rope<float, float>(const float *A, const float *W, int M, 
                                          float *qkv, const RopeOut<float> &ro,
                                          const TreeMeta &meta, int B, const GemmAux &aux,
                                          hipStream_t s) {
-  hipError_t e = launch_gemm<float, float>(EPI_F32, A, W, M, N, K, nullptr, qkv, aux, s);
+  const RowsPlan p = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap, 4);
+  float *dst = p.nsl > 1 ? aux.part : qkv;
+  launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, dst, p, 0);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_rope_kv<float>(qkv, 1, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
-                               ro.capacity, ro.rot, s);
+  return launch_rope_kv<float>(dst, p.nsl, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv,
+                               ro.hd, ro.capacity, ro.rot, s);
 }
 
 template <>
@@ -1394,7 +1366,7 @@ hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, 
   *ntile = 0;
   if (tile_max && rows_ok(EPI_F32_MAX, M, N, K, aux.packed)) {
     const RowsPlan mp = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0);
-    launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, nullptr, logits, mp, aux.packed, tile_max);
+    launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (f16 *)nullptr, logits, mp, aux.packed, tile_max);
     *ntile = mp.nt;
     return hipGetLastError();
   }
@@ -1417,10 +1389,14 @@ hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, 
 
 template <>
 hipError_t launch_lm_head<float, float>(const float *A, const float *W, int M, int N, int K,
-                                        float *logits, float *, int *ntile, const GemmAux &aux,
-                                        hipStream_t s) {
+                                        float *logits, float *tile_max, int *ntile,
+                                        const GemmAux &aux, hipStream_t s) {
   *ntile = 0;
-  return launch_gemm<float, float>(EPI_F32, A, W, M, N, K, nullptr, logits, aux, s);
+  if (!tile_max) return launch_gemm<float, float>(EPI_F32, A, W, M, N, K, nullptr, logits, aux, s);
+  const RowsPlan p = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0, 4);
+  launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (float *)nullptr, logits, p, 0, tile_max);
+  *ntile = p.nt;
+  return hipGetLastError();
 }
 
 }  // namespace acespec

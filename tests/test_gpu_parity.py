@@ -99,6 +99,18 @@ def test_tree_row_counts(B, depth, d, F, packed):
     _check_tree(run, tol=2e-2)
 
 
+@pytest.mark.parametrize("B, depth, kw", [
+    (1, 0, dict()), (2, 7, dict(d=64, F=64, H=1, Hkv=1, V=100)), (1, 16, dict(d=1024, F=2048)),
+    (3, 20, dict(hd=128, H=2, Hkv=1, S=600)), (3, 48, dict(hd=128, H=4, Hkv=4, S=255, V=20004)),
+    (5, 59, dict(S=30)), (2, 11, dict(d=8256, F=128, V=1000))])
+def test_tree_fp32_shapes(B, depth, kw):
+    """The fp32 model away from its one configuration: 1 to 300 rows (one to three row tiles
+    of the GEMM), widths with one k unit and many, prefixes over several blocks of slots, a
+    width beyond the fused residual norm, a vocabulary whose rows are split."""
+    w = small_bf16(**dict(dict(dtype="f32", B=B, tree="chain", depth=depth, S=137, V=3004), **kw))
+    _check_tree(hz.run_tree(w), tol=1e-4)
+
+
 def test_pack_weight_layout_matches_its_definition():
     """acespec_pack_weight against the layout written out on the host: 16-byte unit
     u = (nb * cols/32 + kt) * 64 + l holds row nb*16 + l%16, columns kt*32 + (l/16)*8 .. +8,
