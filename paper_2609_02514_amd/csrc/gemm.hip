@@ -81,6 +81,8 @@ constexpr int epi_smem(int epi, int tbm, int tbn, int wnn) {
 //   whose accumulators are summed through LDS before the epilogue: two waves a SIMD for
 //   a product with fewer tiles than CUs, without fp32 partials in memory (QKV + RoPE
 //   epilogue only).  KSS = 64.
+// PK = 3: packed weights staged through LDS with the activations, each 1 KB fragment one DMA
+//   read back without conflicts, so that the waves of a column share one load of it.
 template <int EPI, typename TB, int WMN, int WNN, int WTM, int WTN, int NST, int OCC, int KSS,
           int PK>
 __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_f16w_kernel(
@@ -91,26 +93,27 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
   constexpr int NW = WMN * WNN * KG;
   constexpr int TBM = WMN * WTM * 16, TBN = WNN * WTN * 16;
   constexpr int ROWB = KSS * 2, PIECES = KSS / 8, ROWS_PER_BLK = 1024 / ROWB;
-  constexpr int A_BYTES = TBM * ROWB, B_BYTES = PK ? 0 : TBN * ROWB;
+  constexpr bool PKR = PK == 1 || PK == 2;   // packed weights straight to registers
+  constexpr int A_BYTES = TBM * ROWB, B_BYTES = PKR ? 0 : TBN * ROWB;
   constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   // 1 KB DMA blocks of the A tile per wave (rounded up: a wave past the last block loads
   // the last block again, the same bytes to the same place, so every wave issues the same
   // number of loads and the vmcnt arithmetic below holds for all of them)
   constexpr int A_BLKS = A_BYTES / 1024, A_DMA = (A_BLKS + NW - 1) / NW;
-  constexpr int B_DMA = B_BYTES / 1024 / NW;
+  constexpr int B_BLKS = B_BYTES / 1024, B_DMA = B_BLKS / NW;
   constexpr int L_DMA = A_DMA + B_DMA;
   constexpr int KSUB = KSS / 32;            // 32-wide MFMA k steps per stage
   constexpr int F = KSUB * WTM;             // A fragments per stage, in use order
   static_assert(A_BLKS * 1024 == A_BYTES && B_DMA * 1024 * NW == B_BYTES, "DMA split");
   static_assert(F >= 4 && NST >= 3, "pipeline shape");
-  static_assert(!PK || KSS == 32 * KG, "packed weights come in 32-wide k steps, one a group");
+  static_assert(!PKR || KSS == 32 * KG, "packed weights come in 32-wide k steps, one a group");
   static_assert(KG == 1 || EPI == acespec::EPI_QKV_ROPE, "split wave groups: QKV epilogue only");
   constexpr int HALF = WTN / 2;  // SwiGLU: gate blocks, then the matching up blocks
   constexpr int RING = NST * STAGE_BYTES, EPI_SM = epi_smem(EPI, TBM, TBN, WNN);
   constexpr int RED = KG > 1 ? WMN * WNN * WTM * WTN * 4 * 64 * 4 : 0;  // group-sum buffer
   constexpr int SM1 = RING > EPI_SM ? RING : EPI_SM;
   __shared__ __attribute__((aligned(1024))) char smem[SM1 > RED ? SM1 : RED];
-  typedef typename Vec8<TB>::type tbx8;
+  typedef typename Vec8<typename std::conditional<PK == 3, f16, TB>::type>::type tbx8;
 
   // Units: `full` whole tiles, then tsplit k-slices of each remaining tile (their partial
   // sums go to `part`, summed by tile_fixup_kernel).  Each group is dealt over the XCDs on
@@ -161,10 +164,19 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
     const int r0 = m0 + blk / KSUB * 16, rl = min(max(M - r0, 0), 16);
     va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % KSUB * 4 + lk) * rl + lr) * 8) * 2
                     : (uint32_t)M * K * 2;
-    sa[t] = rl * ROWB;
+    sa[t] = __builtin_amdgcn_readfirstlane(rl * ROWB);
   }
 #pragma unroll
   for (int t = 0; t < B_DMA; ++t) {
+    if constexpr (PK == 3) {  // fragment (16-row block j / KSUB, k step j % KSUB)
+      const int j = w * B_DMA + t, blk = j / KSUB;
+      const int c = EPI == acespec::EPI_SWIGLU
+                        ? min(tn * (TBN / 2) + blk % (TBN / 32) * 16, N - 16) +
+                              (blk < TBN / 32 ? 0 : N)
+                        : min(tn * TBN + blk * 16, N - 16);
+      vb[t] = (uint32_t)c * K * 2 + j % KSUB * 1024 + lane * 16;
+      continue;
+    }
     const int row = (w * B_DMA + t) * ROWS_PER_BLK + drow;  // W-tile row
     int wr;
     if (EPI == acespec::EPI_SWIGLU) {
@@ -179,8 +191,8 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
   }
   // Packed weights: fragment (16-row block nb, k step kt) at ((nb * KT + kt) * 64 + lane)
   // 16-byte units; the wave's WTN column blocks, SwiGLU-paired like the LDS path's rows.
-  const f16x8 *pkw[PK ? WTN : 1];
-  if constexpr (PK) {
+  const f16x8 *pkw[PKR ? WTN : 1];
+  if constexpr (PKR) {
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
       int c, base;
@@ -204,7 +216,8 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
     }
 #pragma unroll
     for (int t = 0; t < B_DMA; ++t)
-      buf_dma16(rsb, (lds_ptr_t)(base + A_BYTES + (w * B_DMA + t) * 1024), vb[t], kt * ROWB);
+      buf_dma16(rsb, (lds_ptr_t)(base + A_BYTES + (w * B_DMA + t) * 1024), vb[t],
+                kt * (PK == 3 ? KSUB * 1024 : ROWB));
   };
 
   // Fragment byte offsets within a stage: A fragment f = (k step f / WTM, row block
@@ -220,7 +233,9 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
                                      : TBN / 2 + wn * HALF * 16 + (j - HALF) * 16) + lr
                          : wn * WTN * 16 + j * 16 + lr;
 #pragma unroll
-    for (int s2 = 0; s2 < KSUB; ++s2) boff[s2][j] = A_BYTES + piece_off<ROWB>(brow, s2 * 4 + lk);
+    for (int s2 = 0; s2 < KSUB; ++s2)
+      boff[s2][j] = A_BYTES + (PK == 3 ? ((brow >> 4) * KSUB + s2) * 1024 + lane * 16
+                                       : piece_off<ROWB>(brow, s2 * 4 + lk));
   }
 
   f32x4 acc[WTM][WTN];
@@ -229,7 +244,7 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
 #pragma unroll
     for (int j = 0; j < WTN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  if constexpr (PK) {
+  if constexpr (PKR) {
     // Step i: A k-tile i sits in ring slot i % NST, its weight fragments in register set
     // i % NST (the loop is unrolled NST times so the set index is static).  At the top of
     // a step this wave's loads of step i have landed (NST - 2 newer steps may be out);
@@ -693,7 +708,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const TA *__restrict_
       const int r0 = m0 + blk / 2 * 16, rl = blk < ABLK ? min(max(M - r0, 0), 16) : 0;
       va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2
                       : (uint32_t)M * K * 2;
-      sa[t] = rl * 128;
+      sa[t] = __builtin_amdgcn_readfirstlane(rl * 128);
     }
   }
   // Weights, as a buffer over the tile's panel (two panels for SwiGLU: gate, up).  Packed:
@@ -965,17 +980,16 @@ constexpr GemmVariant kVariants[] = {
     {2, 2, 4, 4, 4, 2, 32, 0},  // 1: 128 x 128, 4 waves of 64 x 64, 64 KB LDS, 2 WGs per CU
     {2, 4, 4, 4, 3, 1, 64, 0},  // 2: 128 x 256, 8 waves of 64 x 64, k 64, 144 KB LDS, 1 WG per CU
     {2, 4, 8, 4, 4, 1, 32, 0},  // 3: 256 x 256, 8 waves of 128 x 64, 128 KB LDS, 1 WG per CU
-    {2, 2, 9, 2, 3, 1, 64, 0},  // 4: 288 x 64, 4 waves of 144 x 32, k 64, 132 KB LDS, 1 WG per CU
     // packed weights (registers fed straight from the fragment-ordered copy):
-    {1, 4, 8, 4, 4, 2, 32, 1},  // 5: 128 x 256, 4 waves of 128 x 64, 32 KB ring, 2 WGs per CU
-    {2, 4, 8, 4, 4, 1, 32, 1},  // 6: 256 x 256, 8 waves of 128 x 64, 64 KB ring, 1 WG per CU
-    {2, 2, 4, 4, 4, 2, 32, 1},  // 7: 128 x 128, 4 waves of 64 x 64, 32 KB ring, 2 WGs per CU
-    {2, 2, 9, 2, 4, 1, 32, 1},  // 8: 288 x 64, 4 waves of 144 x 32, 72 KB ring, 1 WG per CU
-    {1, 4, 8, 4, 4, 1, 64, 2},  // 9: 128 x 256, two groups of 4 waves of 128 x 64 splitting k
-    {2, 2, 4, 4, 4, 1, 64, 2},  // 10: 128 x 128, two groups of 4 waves of 64 x 64 splitting k
-    {1, 8, 8, 4, 4, 1, 32, 1},  // 11: 128 x 512, 8 waves of 128 x 64, 32 KB ring, 1 WG per CU
-    {1, 8, 4, 4, 4, 1, 32, 1},  // 12: 64 x 512, 8 waves of 64 x 64, 16 KB ring, 1 WG per CU
-    {1, 4, 7, 4, 4, 1, 64, 2},  // 13: 112 x 256, two groups of 4 waves of 112 x 64 splitting k
+    {1, 4, 8, 4, 4, 2, 32, 1},  // 4: 128 x 256, 4 waves of 128 x 64, 32 KB ring, 2 WGs per CU
+    {2, 4, 8, 4, 4, 1, 32, 1},  // 5: 256 x 256, 8 waves of 128 x 64, 64 KB ring, 1 WG per CU
+    {2, 2, 4, 4, 4, 2, 32, 1},  // 6: 128 x 128, 4 waves of 64 x 64, 32 KB ring, 2 WGs per CU
+    {1, 4, 8, 4, 4, 1, 64, 2},  // 7: 128 x 256, two groups of 4 waves of 128 x 64 splitting k
+    {2, 2, 4, 4, 4, 1, 64, 2},  // 8: 128 x 128, two groups of 4 waves of 64 x 64 splitting k
+    {1, 8, 8, 4, 4, 1, 32, 1},  // 9: 128 x 512, 8 waves of 128 x 64, 32 KB ring, 1 WG per CU
+    {1, 8, 4, 4, 4, 1, 32, 1},  // 10: 64 x 512, 8 waves of 64 x 64, 16 KB ring, 1 WG per CU
+    {1, 4, 7, 4, 4, 1, 64, 2},  // 11: 112 x 256, two groups of 4 waves of 112 x 64 splitting k
+    {2, 4, 9, 4, 4, 1, 32, 3},  // 12: 288 x 256, 8 waves of 144 x 64, weights through LDS, 136 KB
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -1049,7 +1063,8 @@ void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N,
     if constexpr (kVariants[V].pk != 2 || EPI == acespec::EPI_QKV_ROPE)                     \
       launch_variant<EPI, V, TB>(s, A, W, M, N, K, out, outf, part, mt, nt, sp, ro, tmax);  \
     break;
-    CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13)
+    CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10)
+    CASE(11) CASE(12)
 #undef CASE
     default: break;
   }
@@ -1058,9 +1073,8 @@ void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N,
 // Default tiling per shape (measured on MI355X): 128 x 128 tiles for few rows (more
 // tiles to spread over 256 CUs), the 8-wave 64-wide-k tiling for QKV-sized fp32
 // outputs, 256 x 256 tiles (a third fewer operand bytes per flop, two stages in flight)
-// for the residual and LM-head products once there are enough rows, 128 x 256 otherwise
-// (for the gate/up product at ~1k rows both tilings measure the same, the 256 x 256 one
-// only with its last round sliced).
+// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms),
+// 128 x 256 otherwise.
 int pick_variant(int epi, int M, int N, int K, int packed) {
   if (packed) {
     // measured on MI355X in the verify steps (272 - 4096 rows).  What sets these products'
@@ -1068,22 +1082,31 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     // eight waves shares its activation rows across twice the columns of a 256-column
     // one (40 instead of 48 KB a CU per k-step at 128 rows), so from ~500 rows the
     // products take 128 x 512 tiles (64 x 512 for the residual product with a short K
-    // at ~520 rows, where 128-row tiles leave most of a last round empty); few-row
-    // batches keep 288 x 64 tiles for the gate/up product and 128 x 128 ones otherwise
-    if (epi == EPI_SWIGLU) return M <= 288 ? 8 : 11;
-    if (M <= 384) return 7;
-    if (epi == EPI_RESID) return K < 8192 && M <= 640 ? 12 : 11;
-    if (M >= 512 && N >= 16384) return 11;
-    if (M >= 2048) return 6;
-    return 5;
+    // at ~520 rows, where 128-row tiles leave most of a last round empty); fewer rows take
+    // 128 x 128 ones (and up to 288 rows most products run in gemm_rows_kernel).
+    if (epi == EPI_SWIGLU || N >= 16384) {
+      // 288 x 256 tiles with the weights through LDS where their row padding and last
+      // round waste less: one workgroup a CU either way, a round costs its tile's area
+      // (520 rows, us: gate/up 112 against 122, LM head 269 against 293; level at 1088 rows
+      // of the LM head, 4 % slower at 4096, where 128 x 512 tiles are picked).  Their
+      // offsets into the weights are 32 bits.
+      const long long cols = epi == EPI_SWIGLU ? 2ll * N : N;
+      auto cost = [&](int tbm, int tbn) {
+        const long long tiles = (M + tbm - 1) / tbm * ((cols + tbn - 1) / tbn);
+        return (tiles + 255) / 256 * tbm * tbn;
+      };
+      if (cols * K < (1ll << 31) && cost(288, 256) < cost(128, 512)) return 12;
+    }
+    if (epi == EPI_SWIGLU) return 9;
+    if (M <= 384) return 6;
+    if (epi == EPI_RESID) return K < 8192 && M <= 640 ? 10 : 9;
+    if (M >= 512 && N >= 16384) return 9;
+    if (M >= 2048) return 5;
+    return 4;
   }
-  // gate/up with up to 288 rows (a 16-session 1B-class batch: 272): one tile spans every
-  // row, so each weight panel is read once and the product is one tile per CU (10 % faster
-  // there; for the residual products, which are sliced along K, it measured slower)
-  if (M <= 288 && epi == EPI_SWIGLU) return 4;
   if (M <= 384) return 1;
   if (epi == EPI_F32 && N <= 8192) return 2;
-  if (M >= 1024 && epi != EPI_SWIGLU) return 3;
+  if (M >= 1024) return 3;
   return 0;
 }
 
@@ -1172,7 +1195,7 @@ hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 
                                float *part, long long part_cap, int cus, hipStream_t s,
                                int packed) {
   if (var < 0) var = pick_variant(epi, M, N, K, packed);
-  if (var >= kNumVariants || kVariants[var].pk != (packed ? 1 : 0)) return hipErrorInvalidValue;
+  if (var >= kNumVariants || (kVariants[var].pk != 0) != (packed != 0)) return hipErrorInvalidValue;
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
   const int mt = (M + tbm - 1) / tbm;
@@ -1236,7 +1259,7 @@ hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M,
     launch_resid_norm_fixup<VV, bf16>(s, aux.part, x, gain, out, M, N, mt, sp.tsplit, eps); \
     break;                                                                                  \
   }
-    CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(11) CASE(12)
+    CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(9) CASE(10)
 #undef CASE
     default: return hipErrorInvalidValue;
   }
@@ -1317,7 +1340,7 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
     // with about one tile a CU), RoPE and cache write in the epilogue: 112 x 256 tiles from
     // ~1k rows (1088 rows: 240 tiles for 256 CUs and 32 padding rows, against 216 tiles and
     // 64 rows at 128 x 256), 128 x 128 below
-    const int gv = M >= 1024 ? 13 : 10;
+    const int gv = M >= 1024 ? 11 : 8;
     const GemmVariant g = kVariants[gv];
     const int mt = (M + g.wtm * 16 * g.wmn - 1) / (g.wtm * 16 * g.wmn);
     const int nt = (N + g.wtn * 16 * g.wnn - 1) / (g.wtn * 16 * g.wnn);
@@ -1327,7 +1350,7 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
       return hipGetLastError();
     }
   }
-  const int var = aux.packed ? (M <= 384 ? 7 : 5) : pick_variant(EPI_F32, M, N, K, 0);
+  const int var = aux.packed ? (M <= 384 ? 6 : 4) : pick_variant(EPI_F32, M, N, K, 0);
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
   const int mt = (M + tbm - 1) / tbm, nt = (N + tbn - 1) / tbn;

@@ -99,6 +99,16 @@ def test_tree_row_counts(B, depth, d, F, packed):
     _check_tree(run, tol=2e-2)
 
 
+@pytest.mark.parametrize("B, depth, F, V", [(17, 31, 13376, 26640), (9, 31, 576, 66000)])
+def test_tree_wide_tiles(B, depth, F, V):
+    """Packed gate/up and LM-head products whose rows fit 288-row tiles better than 128-row
+    ones (544 rows: two tiles, the second partial; 288 rows: one), with a partial last
+    column tile."""
+    w = small_bf16(F=F, B=B, S=40, tree="chain", depth=depth, V=V, L=1)
+    run = hz.run_tree(w, packed=True)
+    _check_tree(run, tol=2e-2)
+
+
 @pytest.mark.parametrize("B, depth, kw", [
     (1, 0, dict()), (2, 7, dict(d=64, F=64, H=1, Hkv=1, V=100)), (1, 16, dict(d=1024, F=2048)),
     (3, 20, dict(hd=128, H=2, Hkv=1, S=600)), (3, 48, dict(hd=128, H=4, Hkv=4, S=255, V=20004)),
