@@ -84,6 +84,20 @@ AS_DEVICE u64 fixw(float v) { return __float2ull_rn(v * AS_FX_SCALE); }
 // already an integer (>= 2^23) or its rounding is below 2^24, so the value is representable.
 AS_DEVICE float fixw_f(float v) { return rintf(v * AS_FX_SCALE); }
 
+// Four weights' fixed-point masses: below 2^32 each, as nearly always, a conversion each.
+AS_DEVICE void fix4(const float (&e)[4], u64 (&w)[4]) {
+  float f[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) f[j] = fixw_f(e[j]);
+  if (fmaxf(fmaxf(f[0], f[1]), fmaxf(f[2], f[3])) < 4294967296.f) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)f[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = (u64)f[j];
+  }
+}
+
 AS_DEVICE float key_to_f32(uint32_t key) {  // inverse of f32_key
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
@@ -335,6 +349,115 @@ struct RowStream {
   }
 };
 
+// Sum over the 16 lanes of a row, in every lane.
+AS_DEVICE uint32_t row16_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lane ^ 1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lane ^ 2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // half mirror
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // mirror
+  return v;
+}
+AS_DEVICE u64 row16_sum(u64 v) {
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+// 2^40 v as an integer, for v given in units of 2^-40 and already whole.
+AS_DEVICE u64 whole_u64(float f) { return (u64)f; }
+constexpr float SMALL_FX = 268435456.f;   // 2^28
+
+// Segments [sb, se) of a row in which no ids are tied at the thresholds: 16 lanes a
+// segment, four segments a wave and step, so that the sums over lanes cost a sixth of those
+// over a wave.  The masses are the integers that segment_pass adds up: p 2^40 comes straight
+// from the scaled normaliser (scaling by a power of two commutes with the roundings), and
+// masses below 2^-12, nearly all, are added as 32-bit integers, the others of a group of
+// four ids as 64-bit ones.  What bounds the pass is this arithmetic (about 25 instructions
+// an id with the residual, 50 before).
+AS_DEVICE bool segment_pass_untied(const float *z, const float *q, int V, int sb, int se,
+                                   bool resid, const Sel &sel, VTop &sm, u64 *seg_p, u64 *seg_r) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, p16 = lane & 15;
+  const float i_hi = sel.inv_hi * AS_FX_SCALE, i_lo = sel.inv_lo * AS_FX_SCALE;
+  bool badq = false;
+  for (int s0 = sb + wave * 4; s0 < se; s0 += NWV * 4) {
+    const int s = s0 + g, id0 = s * SEG + p16 * 4;
+    const int lim = s < se ? V : 0;
+    float4 z4[4], q4[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int id = id0 + k * 64, ld = id < lim ? id : V - 4;
+      // last pass over the row and its draft q: streamed past L2 and the MALL
+      z4[k] = ld_stream(z + ld);
+      if (resid) q4[k] = ld_stream(q + ld);
+    }
+    uint32_t sp = 0, sr = 0;
+    u64 sp64 = 0, sr64 = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int id = id0 + k * 64;
+      const bool valid = id < lim;
+      const float zz[4] = {z4[k].x, z4[k].y, z4[k].z, z4[k].w};
+      float P[4], R[4];
+      bool top = false;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t key = f32_key(zz[j]);
+        const float f = fixw_f(elem_e(zz[j], sel));
+        P[j] = valid && key >= sel.tau_p ? fmaf(f, i_hi, f * i_lo) : 0.f;
+        top |= key >= sel.tau_k;
+      }
+      if (resid) {
+        const float qq[4] = {q4[k].x, q4[k].y, q4[k].z, q4[k].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          badq |= valid && !(qq[j] >= 0.f && qq[j] <= 3.402823466e38f);
+          R[j] = rintf(fmaxf(fmaf(qq[j], -AS_FX_SCALE, P[j]), 0.f));
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) P[j] = rintf(P[j]);
+      if (fmaxf(fmaxf(P[0], P[1]), fmaxf(P[2], P[3])) < SMALL_FX) {
+        sp += ((uint32_t)P[0] + (uint32_t)P[1]) + ((uint32_t)P[2] + (uint32_t)P[3]);
+        if (resid) sr += ((uint32_t)R[0] + (uint32_t)R[1]) + ((uint32_t)R[2] + (uint32_t)R[3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          sp64 += whole_u64(P[j]);
+          if (resid) sr64 += whole_u64(R[j]);
+        }
+      }
+      if (top && valid) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t key = f32_key(zz[j]);
+          if (key >= sel.tau_k) {
+            const uint32_t slot = atomicAdd(&sm.ncand, 1u);
+            if (slot < KMAX) {
+              sm.cand_key[slot] = key;
+              sm.cand_id[slot] = id + j;
+              sm.cand_in[slot] = key >= sel.tau_p ? 1u : 0u;
+            }
+          }
+        }
+      }
+    }
+    u64 tp, tr = 0;
+    if (__ballot((sp64 | sr64) != 0) == 0) {
+      // 16 sums below 2^32: their 16-bit halves add up in 32 bits
+      tp = ((u64)row16_sum(sp >> 16) << 16) + row16_sum(sp & 0xFFFFu);
+      if (resid) tr = ((u64)row16_sum(sr >> 16) << 16) + row16_sum(sr & 0xFFFFu);
+    } else {
+      tp = row16_sum(sp64 + sp);
+      if (resid) tr = row16_sum(sr64 + sr);
+    }
+    if (p16 == 0 && s < se) {
+      seg_p[s] = tp;
+      seg_r[s] = tr;
+    }
+  }
+  return badq;
+}
+
 // Segments [sb, se) of a row, one wave a segment: the fixed-point masses of p_r (seg_p) and
 // of the residual (seg_r, when resid), and the top-k ids, appended to sm.cand_*.  tie_base
 // gives the number of ids tied at the two thresholds before a segment (asked for only where
@@ -345,6 +468,8 @@ struct RowStream {
 template <typename TieBase>
 AS_DEVICE bool segment_pass(const float *z, const float *q, int V, int sb, int se, bool resid,
                             const Sel &sel, VTop &sm, TieBase tie_base, u64 *seg_p, u64 *seg_r) {
+  if (sel.c_p <= 1 && sel.c_k <= 1)
+    return segment_pass_untied(z, q, V, sb, se, resid, sel, sm, seg_p, seg_r);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool badq = false;
   for (int s0 = sb + wave; s0 < se; s0 += NWV * VU) {
@@ -538,11 +663,16 @@ __global__ __launch_bounds__(VT) void vocab_hist_kernel(acespec::VocabArgs a) {
     for (int u = 0; u < VR; ++u) {
       if (rs.i0 + u * VT * 4 >= i_end) break;
       const float zz[4] = {rs.cur[u].x, rs.cur[u].y, rs.cur[u].z, rs.cur[u].w};
+      float e[4];
+      u64 w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) e[j] = elem_e(zz[j], sel);
+      fix4(e, w);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int b = exp_bin(zz[j], sel.M, sel.c_hi);
         atomicAdd(&cnt[b], 1u);
-        atomicAdd(&mass[b], fixw(elem_e(zz[j], sel)));
+        atomicAdd(&mass[b], w[j]);
       }
     }
   }
@@ -864,7 +994,6 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
   }
   if (tid == 0) sm.ncand = 0;
   __syncthreads();
-  u64 tot = 0;
   for (RowStream rs(z, V, tid * 4); rs.more(); rs.advance()) {
     rs.prefetch();
     const int i0 = rs.i0;
@@ -873,17 +1002,23 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
     for (int u = 0; u < VR; ++u) {
       if (i0 + u * VT * 4 >= V) break;
       const float zz[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
+      float e[4];
+      u64 w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) e[j] = elem_e(zz[j], sel);
+      fix4(e, w);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t key = f32_key(zz[j]);
-        const u64 w = fixw(elem_e(zz[j], sel));
-        tot += w;
         atomicAdd(&sm.h.cnt[key >> 20], 1u);
-        atomicAdd(&sm.h.mass[key >> 20], w);
+        atomicAdd(&sm.h.mass[key >> 20], w[j]);
       }
     }
   }
-  const u64 S_fx = block_sum(tot, sm);  // includes a barrier after the histogram writes
+  __syncthreads();
+  u64 tot = 0;
+  for (int i = tid; i < 4096; i += VT) tot += sm.h.mass[i];
+  const u64 S_fx = block_sum(tot, sm);
   const u64 T_p = nucleus_target(a.top_p, S_fx);
   const u64 K = (u64)a.k;
 
