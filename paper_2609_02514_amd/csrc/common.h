@@ -73,6 +73,20 @@ AS_DEVICE float rows4_sum(float v) {
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
+// Maximum over the 16 lanes of a row, in every lane, by register permutes within the row
+// (LDS-routed shuffles put four LDS latencies into every row of a GEMM epilogue).
+AS_DEVICE float row16_max(float v) {
+#define ROW16_STEP(ctrl)                                                                    \
+  v = fmaxf(v, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(                       \
+                   0, (int)__float_as_uint(v), ctrl, 0xF, 0xF, true)))
+  ROW16_STEP(0xB1);   // lane ^ 1
+  ROW16_STEP(0x4E);   // lane ^ 2
+  ROW16_STEP(0x141);  // half mirror
+  ROW16_STEP(0x140);  // mirror
+#undef ROW16_STEP
+  return v;
+}
+
 AS_DEVICE float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;

@@ -518,8 +518,7 @@ __global__ __launch_bounds__(WMN * WNN * (PK == 2 ? 2 : 1) * 64, OCC) void gemm_
         float m = -INFINITY;
 #pragma unroll
         for (int j = 0; j < WTN; ++j) m = max_or_inf(m, acc[ii][j][e]);
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        m = row16_max(m);
         if (lr == 0) red[wn * TBM + wm * WTM * 16 + ii * 16 + lk * 4 + e] = m;
       }
     __syncthreads();
@@ -874,8 +873,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const TA *__restrict_
           const int col = tn * ROWSN + wn * 32 + j * 16 + lr;
           if (row < M && col < N) outf[(size_t)row * N + col] = v;
         }
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        m = row16_max(m);
         if (lr == 0) mx[wn][lrow] = m;
       }
     }
@@ -1073,8 +1071,9 @@ void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N,
 // Default tiling per shape (measured on MI355X): 128 x 128 tiles for few rows (more
 // tiles to spread over 256 CUs), the 8-wave 64-wide-k tiling for QKV-sized fp32
 // outputs, 256 x 256 tiles (a third fewer operand bytes per flop, two stages in flight)
-// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms),
-// 128 x 256 otherwise.
+// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms) and
+// for the LM head from 129 (65536 ids, us, against 128 x 128 or 128 x 256: 138 rows 151 /
+// 163, 272 rows 209 / 234, 520 rows 309 / 361), 128 x 256 otherwise.
 int pick_variant(int epi, int M, int N, int K, int packed) {
   if (packed) {
     // measured on MI355X in the verify steps (272 - 4096 rows).  What sets these products'
@@ -1087,26 +1086,27 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     if (epi == EPI_SWIGLU || N >= 16384) {
       // 288 x 256 tiles with the weights through LDS where their row padding and last
       // round waste less: one workgroup a CU either way, a round costs its tile's area
-      // (520 rows, us: gate/up 112 against 122, LM head 269 against 293; level at 1088 rows
-      // of the LM head, 4 % slower at 4096, where 128 x 512 tiles are picked).  Their
-      // offsets into the weights are 32 bits.
+      // (520 rows, us: gate/up 112 against 122, LM head of 65536 ids 253 against 302; 272
+      // rows 141 against 202, and 224 in 128 x 128 tiles; level at 1088 rows of the LM head,
+      // 4 % slower at 4096, where 128 x 512 tiles are picked, as at 138 rows: 118, against
+      // 166 in gemm_rows_kernel).  Their offsets into the weights are 32 bits.
       const long long cols = epi == EPI_SWIGLU ? 2ll * N : N;
       auto cost = [&](int tbm, int tbn) {
         const long long tiles = (M + tbm - 1) / tbm * ((cols + tbn - 1) / tbn);
         return (tiles + 255) / 256 * tbm * tbn;
       };
       if (cols * K < (1ll << 31) && cost(288, 256) < cost(128, 512)) return 12;
+      return 9;
     }
-    if (epi == EPI_SWIGLU) return 9;
     if (M <= 384) return 6;
     if (epi == EPI_RESID) return K < 8192 && M <= 640 ? 10 : 9;
-    if (M >= 512 && N >= 16384) return 9;
     if (M >= 2048) return 5;
     return 4;
   }
+  if (N >= 16384 && epi == EPI_F32 && M > 128) return 3;
   if (M <= 384) return 1;
   if (epi == EPI_F32 && N <= 8192) return 2;
-  if (M >= 1024) return 3;
+  if (M >= (epi == EPI_SWIGLU ? 512 : 1024)) return 3;
   return 0;
 }
 
@@ -1147,8 +1147,9 @@ bool rows_ok(int epi, int M, int N, int K, int packed) {
   if (epi == EPI_RESID && M <= kSomeRows && !(packed && (long long)N * K > (32 << 20)))
     return true;
   // the LM head's row-major panels leave LDS for one workgroup a CU beyond 48 rows, whose
-  // logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128 tiles)
-  if (epi == EPI_F32_MAX) return M <= (packed ? 144 : 48);
+  // logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128 tiles);
+  // packed, registers do from 81 rows
+  if (epi == EPI_F32_MAX) return M <= (packed ? 80 : 48);
   return M <= kFewRows;
 }
 
