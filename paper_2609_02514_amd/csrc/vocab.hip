@@ -970,9 +970,12 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
     return;
   }
 
-  if (SPLIT && !split_view(a, row).st->whole) {
+  // (a list that does not hold exactly the top-k ids is not used: its other slots are an
+  // earlier call's)
+  const RowState *st0 = SPLIT ? split_view(a, row).st : nullptr;
+  if (SPLIT && !st0->whole && st0->ntop == (uint32_t)a.k) {
     const SplitView v = split_view(a, row);
-    const RowState &st = *v.st;
+    const RowState &st = *st0;
     sel = st.sel;
     for (int s = tid; s < nseg; s += VT) {
       sm.g.seg_p[s] = v.seg_p[s];

@@ -338,6 +338,98 @@ def test_tail_split_rows(rows, V, kind):
     _run_tail(w, W=W)
 
 
+def _bin_edge(M, T, b):
+    """The lowest float32 below M whose bin of the split passes (25 to the unit of the base-2
+    exponent) is less than b bins below M's; its lower neighbour is in the next bin down."""
+    c = np.float32(1.4426950408889634 / T)
+    key = lambda z: int(np.float32(z).view(np.int32)) if z >= 0 else \
+        -(int(np.float32(z).view(np.int32)) & 0x7FFFFFFF)
+    val = lambda k: np.int32(k).view(np.float32) if k >= 0 else -np.int32(-k).view(np.float32)
+    lo, hi = key(M - b * T), key(M)          # (lo: outside, hi: inside)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if (np.float32(val(mid) - M) * c) * np.float32(-25.0) < b:
+            hi = mid
+        else:
+            lo = mid
+    return key, val, hi
+
+
+def _adjacent_bin_rows(T, V, n_up, n_down, seed):
+    """Rows of logits whose order around an edge between two bins is decided by single ulps:
+    the maximum, n_up ids from the edge upwards, n_down right below it, one id at the far end
+    of either bin, the others without mass.  Maxima of all sizes, edges at and around zero
+    among them (where floats are densest)."""
+    rng = np.random.default_rng(seed)
+    b, rows = 3, []
+    for M in [10.0, 0.5, 1.0, 3.0, 40.0, -2.0, -0.3, -25.0, 0.0665, 0.07, 0.06, 0.0662] + \
+            list(rng.uniform(-20, 20, 6)) + list(rng.uniform(0.02, 0.12, 6)):
+        M = np.float32(M)
+        key, val, e = _bin_edge(M, T, b)
+        up_end, down_end = _bin_edge(M, T, b - 1)[2] - 1, _bin_edge(M, T, b + 1)[2]
+        special = [val(up_end)] + [val(e + j) for j in range(n_up)] + \
+            [val(e - 1 - j) for j in range(n_down)] + [val(down_end)]
+        z = (M - np.float32(30.0) - rng.random(V).astype(np.float32)).astype(np.float32)
+        at = rng.choice(V, len(special) + 1, replace=False)
+        z[at] = [M] + special
+        rows.append(z)
+    return np.stack(rows)
+
+
+def _run_given_logits(z, reps, q, draft, u, T, top_p, top_k):
+    """The tail over exactly these logits (fp32 model, LM head z^T, one-hot hidden states),
+    every row reps times over."""
+    from paper_2609_02514_amd.acespec import Verifier
+    n, V = z.shape
+    R, d = n * reps, 64
+    lm = torch.zeros(V, d)
+    lm[:, :n] = torch.from_numpy(z).t()
+    hidden = torch.eye(n, d).repeat(reps, 1).cuda()
+    v = Verifier(0, d, 0, 1, 0, 0, V, "f32", R, 0)
+    outs = v.alloc_outputs(R, R, 1, top_k, V, "cuda", True)
+    dev = lambda t: torch.from_numpy(t).repeat(reps, *([1] * (t.ndim - 1))).cuda()
+    hz.log(f"given logits: R={R} V={V} T={T} top_p={top_p:.6f} top_k={top_k}")
+    v.verify_tail(lm.cuda(), None, hidden, dev(draft), dev(q), dev(u), 1, T, top_p, top_k, outs)
+    torch.cuda.synchronize()
+    v.close()
+    return {k: t.cpu().numpy()[:n] for k, t in outs.items()}
+
+
+@pytest.mark.parametrize("lower", ["top_k"])
+def test_tail_split_rows_thresholds_in_adjacent_bins(lower):
+    """One threshold on the highest id of a bin, the other in the next bin up, a few ulps
+    away: the ids of the upper bin are not part of the lower threshold's search.  Split rows
+    against the ids in sorted order, and against the whole-row kernel (more rows of the same
+    logits than are split), bit for bit."""
+    T, V, n_up, n_down = 0.8, 24000, 8, 6
+    z = _adjacent_bin_rows(T, V, n_up, n_down, 11)
+    n = len(z)
+    order = np.stack([np.lexsort((np.arange(V), -r)) for r in z])
+    zs = np.take_along_axis(z.astype(np.float64), order, 1)
+    p = np.exp((zs - zs[:, :1]) / T)
+    cum = (p.cumsum(1) / p.sum(1, keepdims=True)).mean(0)   # (the same rows to 1e-4)
+    first_down = 2 + n_up            # rank of the highest id of the lower bin
+    if lower == "top_k":
+        top_k, cross = first_down + 1, 3
+    else:
+        top_k, cross = 4, first_down
+    top_p = float(0.5 * (cum[cross - 1] + cum[cross]))
+    rng = np.random.default_rng(5)
+    q = rng.random((n, V)).astype(np.float32)
+    q /= q.sum(1, keepdims=True)
+    draft = order[np.arange(n), rng.integers(0, 12, n)].astype(np.int32)
+    u = rng.uniform(0.01, 0.99, (n, 3)).astype(np.float32)
+    split = _run_given_logits(z, 1, q, draft, u, T, top_p, top_k)
+    whole = _run_given_logits(z, 6, q, draft, u, T, top_p, top_k)
+    assert np.array_equal(split["logits_out"], z) and (split["status"] == 0).all()
+    for g in (whole, split):
+        assert np.array_equal(g["topk_ids"], order[:, :top_k])
+        # ids up to the crossing one carry mass, no others
+        assert ((g["topk_probs"] > 0) == (np.arange(top_k) <= cross)).all()
+    for k in split:
+        assert np.array_equal(split[k], whole[k]), k
+
+
 @pytest.mark.parametrize("T,top_p,top_k", [
     (1.0, 1.0, 256),    # whole vocabulary in the nucleus, the largest payload
     (0.05, 0.9, 1),     # near-greedy target, a one-token payload
