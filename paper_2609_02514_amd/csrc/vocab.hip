@@ -802,8 +802,11 @@ __global__ __launch_bounds__(VT) void vocab_select_kernel(acespec::VocabArgs a) 
     atomicMax(&hi_k, mx_k);
   }
   __syncthreads();
-  // radix steps over key - lo, 11 bits at a time from the top of the bins' key ranges
-  uint32_t bp_lo = lo_p, bk_lo = lo_k, w_p = hi_p - lo_p, w_k = hi_k - lo_k;  // width - 1
+  // radix steps over key - lo, 11 bits at a time from the top of the bins' key ranges; a
+  // step's last sub-range ends at its bin's highest key, for the list holds the other bin's
+  // elements too, and those above this bin are counted in above_* already
+  const uint32_t end_p = hi_p, end_k = hi_k;
+  uint32_t bp_lo = lo_p, bk_lo = lo_k, w_p = end_p - lo_p, w_k = end_k - lo_k;  // width - 1
   u64 above_p = st.ap, above_k = st.ak;
   while (true) {
     const uint32_t w = max(w_p, w_k);
@@ -851,7 +854,8 @@ __global__ __launch_bounds__(VT) void vocab_select_kernel(acespec::VocabArgs a) 
       sel.inv_lo = (float)(inv - (double)sel.inv_hi);
       break;
     }
-    w_p = w_k = (1u << sh) - 1;
+    w_p = min((1u << sh) - 1, end_p - bp_lo);
+    w_k = min((1u << sh) - 1, end_k - bk_lo);
   }
   const bool many = sel.c_p > TIES || sel.c_k > TIES;
   if (tid == 0) {

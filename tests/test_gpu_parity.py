@@ -395,7 +395,7 @@ def _run_given_logits(z, reps, q, draft, u, T, top_p, top_k):
     return {k: t.cpu().numpy()[:n] for k, t in outs.items()}
 
 
-@pytest.mark.parametrize("lower", ["top_k"])
+@pytest.mark.parametrize("lower", ["top_k", "top_p"])
 def test_tail_split_rows_thresholds_in_adjacent_bins(lower):
     """One threshold on the highest id of a bin, the other in the next bin up, a few ulps
     away: the ids of the upper bin are not part of the lower threshold's search.  Split rows
