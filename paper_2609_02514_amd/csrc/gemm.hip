@@ -688,7 +688,10 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const TA *__restrict_
   const int U = K * ES >> 7;                  // units: 128 bytes of a row
   const int u0 = (int)((long long)U * sl / nsl), u1 = (int)((long long)U * (sl + 1) / nsl);
 
-  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A, (uint32_t)((size_t)M * K * ES));
+  // activations, as a buffer over the tile's rows: 32-bit offsets hold for any M
+  const int mrows = min(M - m0, TBM);
+  const uint32_t abytes = (uint32_t)mrows * K * ES;
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(A + (size_t)m0 * K, abytes);
   uint32_t va[A_DMA];
   int sa[A_DMA], lb[A_DMA];
 #pragma unroll
@@ -698,15 +701,14 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(const TA *__restrict_
     const int blk = w + t * 8;
     lb[t] = blk * 1024;
     if (F32) {   // row-major: 8 rows x 128 bytes a block, swizzled like the weights
-      const int lrow = blk * 8 + (lane >> 3), r = m0 + lrow;
-      va[t] = blk < ABLK && r < M
-                  ? (uint32_t)r * K * 4 + (((lane & 7) ^ ((lrow >> 1) & 7)) << 4)
-                  : (uint32_t)M * K * 4;
+      const int r = blk * 8 + (lane >> 3);
+      va[t] = blk < ABLK && r < mrows
+                  ? (uint32_t)r * K * 4 + (((lane & 7) ^ ((r >> 1) & 7)) << 4)
+                  : abytes;
       sa[t] = 128;
     } else {
-      const int r0 = m0 + blk / 2 * 16, rl = blk < ABLK ? min(max(M - r0, 0), 16) : 0;
-      va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2
-                      : (uint32_t)M * K * 2;
+      const int r0 = blk / 2 * 16, rl = blk < ABLK ? min(max(mrows - r0, 0), 16) : 0;
+      va[t] = lr < rl ? ((uint32_t)r0 * K + ((blk % 2 * 4 + lk) * rl + lr) * 8) * 2 : abytes;
       sa[t] = __builtin_amdgcn_readfirstlane(rl * 128);
     }
   }

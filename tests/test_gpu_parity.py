@@ -338,6 +338,33 @@ def test_tail_split_rows(rows, V, kind):
     _run_tail(w, W=W)
 
 
+def test_tail_fp32_activations_past_4_gib():
+    """The fp32 model's hidden states beyond 2^32 bytes (262344 rows of width 4096), through
+    the allocation-free entry point.  Bound of the logits: 4096 products of unit normals and
+    weights of 0.02, summed in fp32 in any order: below 4096 * 2^-24 of the sum of magnitudes
+    (52), 1.3e-2; about 1e-5 as the errors mostly cancel.  Held to 2e-4."""
+    from paper_2609_02514_amd import acespec as A
+    R, d, V, k = 262144 + 200, 4096, 64, 4
+    g = torch.Generator(device="cuda").manual_seed(3)
+    hidden = torch.randn(R, d, generator=g, device="cuda")
+    lm = torch.randn(V, d, generator=g, device="cuda") * 0.02
+    q = torch.full((R, V), 1.0 / V, device="cuda")
+    u = torch.full((R, 3), 0.5, device="cuda")
+    draft = torch.zeros(R, dtype=torch.int32, device="cuda")
+    outs = A.Verifier.alloc_outputs(R, R, 1, k, V, "cuda", True)
+    hz.log(f"noalloc tail fp32 R={R} d={d} V={V}")
+    A.acespec_verify_tail_noalloc(
+        A.ModelDesc(0, d, 0, 1, 0, 0, V, 1e4, 1e-5, A.ACESPEC_F32), lm.data_ptr(),
+        A.ACESPEC_LAYOUT_ROWS, None, hidden.data_ptr(), draft.data_ptr(), q.data_ptr(),
+        u.data_ptr(), R, 1, A.Params(0.8, 0.9, k), A.Verifier.outputs_struct(outs),
+        torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert (outs["status"] == 0).all()
+    for r0 in (0, 131072 - 100, R - 400):
+        want = hidden[r0:r0 + 400].double() @ lm.double().t()
+        assert (outs["logits_out"][r0:r0 + 400].double() - want).abs().max() < 2e-4, r0
+
+
 def _bin_edge(M, T, b):
     """The lowest float32 below M whose bin of the split passes (25 to the unit of the base-2
     exponent) is less than b bins below M's; its lower neighbour is in the next bin down."""
