@@ -268,10 +268,9 @@ hipError_t launch_qkv_rope(const TA *A, const TW *W, int M, int N, int K, float 
                            const RopeOut<TW> &ro, const TreeMeta &meta, int B,
                            const GemmAux &aux, hipStream_t s);
 
-// The LM head: fp32 logits [M, N] = A . W^T.  When the product is not sliced along K the
-// epilogue also writes tile_max[row * ntile + t], the maximum of row `row` over column
-// tile t, and *ntile is set (else *ntile = 0): the vocabulary kernel then takes a row's
-// maximum from ntile values instead of a pass over the row.
+// The LM head: fp32 logits [M, N] = A . W^T, and tile_max[row * ntile + t], the maximum of
+// row `row` over column tile t (+inf if one of its logits is not finite): the vocabulary
+// kernel takes a row's maximum from these *ntile values instead of a pass over the row.
 template <typename TW, typename TA>
 hipError_t launch_lm_head(const TA *A, const TW *W, int M, int N, int K, float *logits,
                           float *tile_max, int *ntile, const GemmAux &aux, hipStream_t s);

@@ -16,6 +16,7 @@
 // the tree K/V (QKV projection), fp32 residual add followed by the next block's RMSNorm
 // (attention output and MLP down projections), SwiGLU (gate/up projection: each tile
 // holds matching gate and up columns).
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -1073,9 +1074,8 @@ void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N,
 // Default tiling per shape (measured on MI355X): 128 x 128 tiles for few rows (more
 // tiles to spread over 256 CUs), the 8-wave 64-wide-k tiling for QKV-sized fp32
 // outputs, 256 x 256 tiles (a third fewer operand bytes per flop, two stages in flight)
-// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms) and
-// for the LM head from 129 (65536 ids, us, against 128 x 128 or 128 x 256: 138 rows 151 /
-// 163, 272 rows 209 / 234, 520 rows 309 / 361), 128 x 256 otherwise.
+// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms),
+// 128 x 256 otherwise.  (The LM head: pick_lm_tiling.)
 int pick_variant(int epi, int M, int N, int K, int packed) {
   if (packed) {
     // measured on MI355X in the verify steps (272 - 4096 rows).  What sets these products'
@@ -1085,14 +1085,11 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     // products take 128 x 512 tiles (64 x 512 for the residual product with a short K
     // at ~520 rows, where 128-row tiles leave most of a last round empty); fewer rows take
     // 128 x 128 ones (and up to 288 rows most products run in gemm_rows_kernel).
-    if (epi == EPI_SWIGLU || N >= 16384) {
+    if (epi == EPI_SWIGLU) {
       // 288 x 256 tiles with the weights through LDS where their row padding and last
       // round waste less: one workgroup a CU either way, a round costs its tile's area
-      // (520 rows, us: gate/up 112 against 122, LM head of 65536 ids 253 against 302; 272
-      // rows 141 against 202, and 224 in 128 x 128 tiles; level at 1088 rows of the LM head,
-      // 4 % slower at 4096, where 128 x 512 tiles are picked, as at 138 rows: 118, against
-      // 166 in gemm_rows_kernel).  Their offsets into the weights are 32 bits.
-      const long long cols = epi == EPI_SWIGLU ? 2ll * N : N;
+      // (520 rows: 112 us against 122).  Their offsets into the weights are 32 bits.
+      const long long cols = 2ll * N;
       auto cost = [&](int tbm, int tbn) {
         const long long tiles = (M + tbm - 1) / tbm * ((cols + tbn - 1) / tbn);
         return (tiles + 255) / 256 * tbm * tbn;
@@ -1105,7 +1102,6 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     if (M >= 2048) return 5;
     return 4;
   }
-  if (N >= 16384 && epi == EPI_F32 && M > 128) return 3;
   if (M <= 384) return 1;
   if (epi == EPI_F32 && N <= 8192) return 2;
   if (M >= (epi == EPI_SWIGLU ? 512 : 1024)) return 3;
@@ -1148,11 +1144,92 @@ bool rows_ok(int epi, int M, int N, int K, int packed) {
   if (K % 64 != 0 || N % 16 != 0) return false;
   if (epi == EPI_RESID && M <= kSomeRows && !(packed && (long long)N * K > (32 << 20)))
     return true;
-  // the LM head's row-major panels leave LDS for one workgroup a CU beyond 48 rows, whose
-  // logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128 tiles);
-  // packed, registers do from 81 rows
-  if (epi == EPI_F32_MAX) return M <= (packed ? 80 : 48);
   return M <= kFewRows;
+}
+
+// The LM head's tiling: the candidate with the smallest estimate.  A 64-wide k step takes a
+// workgroup alone on its CU `one` us and two of them `two` (-1: gemm_rows_kernel, for its
+// least row tile; `row` more per further 16 rows), and the last round of workgroups counts
+// whole; nothing goes faster than the weights' stream (`tbs` TB/s, less where fewer than 0.6
+// of the CUs pull it, and `again` of it more for each further row tile, whose panels the
+// L2s do not all share); the logits cost `store` us a MB.  Fitted to 1 .. 2048 rows of 4096
+// .. 152064 ids, width 2048 .. 8192 (6 to 8 % off a time); the pick is 1.4 % (packed) and
+// 0.4 % off the best candidate on average.  Whole thresholds on the rows, as the other products have, miss what the
+// vocabulary does to the rounds: packed at 96 rows of 16384 ids, width 4096, 128 x 512 tiles
+// (32 of them) take 98 us, 128 x 128 49; at 96 rows of 98304 ids 162 and 174.
+struct LmTiling {
+  int var;
+  float one, row, two, store, tbs, again;
+};
+constexpr LmTiling kLmPacked[] = {
+    {-1, 0.50f, 0.02f, 0.96f, 0.41f, 6.24f, 0.f},
+    {6, 0.64f, 0.f, 1.03f, 0.22f, 5.00f, 0.50f},
+    {4, 0.92f, 0.f, 1.56f, 0.25f, 5.15f, 0.30f},
+    {9, 1.36f, 0.f, 0.f, 0.31f, 5.30f, 0.20f},
+    {12, 1.52f, 0.f, 0.f, 0.36f, 4.90f, 0.44f},
+};
+constexpr LmTiling kLmRows[] = {
+    {-1, 0.70f, 0.01f, 0.99f, 0.70f, 5.07f, 0.f},
+    {1, 0.80f, 0.f, 1.09f, 0.31f, 4.53f, 0.40f},
+    {0, 1.46f, 0.f, 1.85f, 0.29f, 3.89f, 0.20f},
+    {3, 1.41f, 0.f, 0.f, 0.33f, 4.02f, 0.50f},
+};
+// gemm_rows_kernel's LM head: beyond 48 row-major rows its panels leave LDS for one workgroup
+// a CU, whose logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128
+// tiles); packed, registers do from 81 rows.
+constexpr int kLmRowsPacked = 80, kLmRowsRows = 48;
+
+SplitPlan plan_lm(int var, int M, int N, int K, int cus, long long part_cap) {
+  const GemmVariant v = kVariants[var];
+  const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
+  const int tiles = (M + tbm - 1) / tbm * ((N + tbn - 1) / tbn);
+  const SplitPlan sp = plan_split(M, N, K, v.kss, tbm, tbn, tiles, cus, v.occ, part_cap);
+  // the row maxima of sliced tiles are reduced by tbn / 4 lanes of one wave: wider tiles
+  // stay whole (at most part of a last round idles)
+  return sp.tsplit > 1 && tbn / 4 > 64 ? SplitPlan{tiles, 1} : sp;
+}
+
+// -1: gemm_rows_kernel.
+int pick_lm_tiling(int M, int N, int K, int packed, int cus, long long part_cap) {
+  double best = 1e30;
+  int pick = 0;
+  auto estimate = [&](const LmTiling &t) {
+    const double mb = (double)N * K * 2e-6;   // the weights
+    double rounds, extra = 0.0;
+    int mt = 1, wgs;
+    auto round_us = [&](int n, double one, double two, int occ) {
+      if (occ == 1) return (n + cus - 1) / cus * one;
+      const int rest = n % (2 * cus);
+      return n / (2 * cus) * two + (rest == 0 ? 0.0 : rest <= cus ? one : two);
+    };
+    if (t.var < 0) {
+      if (M > (packed ? kLmRowsPacked : kLmRowsRows) || K % 64 || N % 16) return;
+      const RowsPlan p = plan_rows(EPI_F32_MAX, M, N, K, cus, 0);
+      const double more = t.row * p.mb;   // (five row blocks: one workgroup as two)
+      wgs = p.mt * p.nt;
+      rounds = round_us(wgs, more + (p.mb <= 3 ? t.one : 0.75), more + t.two, 2);
+    } else {
+      const GemmVariant v = kVariants[t.var];
+      const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
+      mt = (M + tbm - 1) / tbm;
+      if (v.pk == 3 && (long long)N * K >= 1ll << 31) return;   // (32-bit weight offsets)
+      const SplitPlan sp = plan_lm(t.var, M, N, K, cus, part_cap);
+      const int tiles = mt * ((N + tbn - 1) / tbn), rest = tiles - sp.full;
+      wgs = sp.full + rest * sp.tsplit;
+      rounds = round_us(sp.full, t.one, t.two, v.occ);
+      if (sp.tsplit > 1) {
+        rounds += round_us(rest * sp.tsplit, t.one, t.two, v.occ) / sp.tsplit;
+        extra = 4.0 + 1.6e-6 * rest * sp.tsplit * tbn * M / mt;   // the fp32 sums' round trip
+      }
+    }
+    const double us = std::max(mb * (1.0 + t.again * (mt - 1)) / (t.tbs * std::min(1.0, 1.7 * wgs / cus)),
+                               K / 64 * rounds) +
+                      t.store * M * N * 4e-6 + extra;
+    if (us < best) { best = us; pick = t.var; }
+  };
+  if (packed) for (const LmTiling &t : kLmPacked) estimate(t);
+  else for (const LmTiling &t : kLmRows) estimate(t);
+  return pick;
 }
 
 template <int EPI, typename TA, typename TW>
@@ -1389,26 +1466,19 @@ template <>
 hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, int K,
                                      float *logits, float *tile_max, int *ntile,
                                      const GemmAux &aux, hipStream_t s) {
-  *ntile = 0;
-  if (tile_max && rows_ok(EPI_F32_MAX, M, N, K, aux.packed)) {
+  const int var = pick_lm_tiling(M, N, K, aux.packed, aux.cus, aux.part_cap);
+  if (var < 0) {
     const RowsPlan mp = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0);
     launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (f16 *)nullptr, logits, mp, aux.packed, tile_max);
     *ntile = mp.nt;
     return hipGetLastError();
   }
-  const int var = pick_variant(EPI_F32, M, N, K, aux.packed);
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
   const int mt = (M + tbm - 1) / tbm, nt = (N + tbn - 1) / tbn;
-  SplitPlan sp = plan_split(M, N, K, v.kss, tbm, tbn, mt * nt, aux.cus, v.occ, aux.part_cap);
-  if (tile_max == nullptr)
-    return launch_f16w_variant<bf16>(var, 0, EPI_F32, A, W, M, N, K, nullptr, logits, aux.part,
-                                     aux.part_cap, aux.cus, s, aux.packed);
-  // the row maxima of sliced tiles are reduced by tbn / 4 lanes of one wave: wider tiles
-  // stay whole (at most part of a last round idles)
-  if (sp.tsplit > 1 && tbn / 4 > 64) sp = SplitPlan{mt * nt, 1};
-  launch_epi<EPI_F32_MAX, bf16>(var, s, A, W, M, N, K, nullptr, logits, aux.part, mt, nt, sp,
-                                RopeOut<bf16>{}, tile_max);
+  launch_epi<EPI_F32_MAX, bf16>(var, s, A, W, M, N, K, nullptr, logits, aux.part, mt, nt,
+                                plan_lm(var, M, N, K, aux.cus, aux.part_cap), RopeOut<bf16>{},
+                                tile_max);
   *ntile = nt;
   return hipGetLastError();
 }
@@ -1417,8 +1487,6 @@ template <>
 hipError_t launch_lm_head<float, float>(const float *A, const float *W, int M, int N, int K,
                                         float *logits, float *tile_max, int *ntile,
                                         const GemmAux &aux, hipStream_t s) {
-  *ntile = 0;
-  if (!tile_max) return launch_gemm<float, float>(EPI_F32, A, W, M, N, K, nullptr, logits, aux, s);
   const RowsPlan p = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0, 4);
   launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (float *)nullptr, logits, p, 0, tile_max);
   *ntile = p.nt;

@@ -338,6 +338,53 @@ def test_tail_split_rows(rows, V, kind):
     _run_tail(w, W=W)
 
 
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("rows, V, d, noalloc", [
+    (1, 64, 64, False), (48, 4112, 512, False), (49, 4112, 512, True), (80, 50272, 256, False),
+    (81, 50272, 256, False), (96, 4112, 4096, False), (96, 16400, 512, True),
+    (129, 16400, 512, False), (160, 32016, 1024, True), (289, 8208, 2048, False),
+    (300, 32016, 256, False), (513, 16400, 1024, False), (577, 32016, 512, False)])
+def test_lm_head_row_counts(rows, V, d, noalloc, packed):
+    """The LM head's tilings, as its rows and vocabulary pick them: whole and sliced tiles of
+    each size with a partial last row and column tile.  Logits against float64: a product of
+    exact 16-bit inputs, d terms summed in fp32 in any order, each of magnitude 0.05 (d terms:
+    their rounding errors, about 2^-24 of the running sum each, stay below d 2^-24 0.05 d^0.5;
+    held to that).  The row maxima, which come from the tiles: the masses of the payload add up
+    to one and the first id is the largest logit."""
+    from paper_2609_02514_amd import acespec as A
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    dt = torch.bfloat16
+    hidden = torch.randn(rows, d, generator=g, device="cuda").to(dt)
+    lm = (torch.randn(V, d, generator=g, device="cuda") * 0.05).to(dt)
+    q = torch.full((rows, V), 1.0 / V, device="cuda")
+    u = torch.full((rows, 3), 0.5, device="cuda")
+    draft = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    outs = A.Verifier.alloc_outputs(rows, rows, 1, 4, V, "cuda", True)
+    w, stream = lm, torch.cuda.current_stream().cuda_stream
+    if packed:
+        w = torch.empty(lm.numel(), dtype=torch.float16, device="cuda")
+        A.acespec_pack_weight(lm.data_ptr(), w.data_ptr(), V, d, stream)
+    hz.log(f"lm head R={rows} V={V} d={d} packed={packed} noalloc={noalloc}")
+    if noalloc:
+        A.acespec_verify_tail_noalloc(
+            A.ModelDesc(0, d, 0, 1, 0, 0, V, 1e4, 1e-5, A.ACESPEC_BF16), w.data_ptr(),
+            A.ACESPEC_LAYOUT_PACKED if packed else A.ACESPEC_LAYOUT_ROWS, None, hidden.data_ptr(),
+            draft.data_ptr(), q.data_ptr(), u.data_ptr(), rows, 1, A.Params(1.0, 0.9, 4),
+            A.Verifier.outputs_struct(outs), stream)
+    else:
+        v = A.Verifier(0, d, 0, 1, 0, 0, V, "bf16", rows, 0)
+        v.verify_tail(w, None, hidden, draft, q, u, 1, 1.0, 0.9, 4, outs, packed=packed)
+        torch.cuda.synchronize()
+        v.close()
+    torch.cuda.synchronize()
+    assert (outs["status"] == 0).all()
+    z = outs["logits_out"]
+    want = hidden.double() @ lm.double().t()
+    assert (z - want).abs().max() < d ** 1.5 * 2.0 ** -24 * 0.05
+    assert torch.equal(z.gather(1, outs["topk_ids"][:, :1].long())[:, 0], z.max(1).values)
+    assert ((outs["topk_probs"].sum(1) - 1).abs() < 1e-5).all()
+
+
 def test_tail_fp32_activations_past_4_gib():
     """The fp32 model's hidden states beyond 2^32 bytes (262344 rows of width 4096), through
     the allocation-free entry point.  Bound of the logits: 4096 products of unit normals and
