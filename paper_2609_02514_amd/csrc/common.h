@@ -290,9 +290,8 @@ hipError_t launch_gemm_resid_norm(const TA *A, const TW *W, int M, int N, int K,
                                   const TW *gain, typename ActOf<TW>::type *out, float eps,
                                   const GemmAux &aux, hipStream_t s);
 
-// The fp16-activation MFMA GEMM (weights TB = bf16, widened to fp16 in registers) with
-// an explicit tiling (var >= 0) and split count (splits_override > 0); var < 0 /
-// splits_override <= 0 choose automatically.
+// The fp16-activation MFMA GEMM (weights TB = bf16, widened to fp16 in registers) in the
+// tiling var, with a split count (splits_override > 0) or the planned one.
 template <typename TB>
 hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 *A,
                                const TB *W, int M, int N, int K, f16 *out, float *outf,

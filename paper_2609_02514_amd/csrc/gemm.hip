@@ -1071,11 +1071,11 @@ void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N,
   }
 }
 
-// Default tiling per shape (measured on MI355X): 128 x 128 tiles for few rows (more
-// tiles to spread over 256 CUs), the 8-wave 64-wide-k tiling for QKV-sized fp32
-// outputs, 256 x 256 tiles (a third fewer operand bytes per flop, two stages in flight)
-// once there are enough rows (32B-class gate/up at 1056 rows: the step 5.09 -> 4.95 ms),
-// 128 x 256 otherwise.  (The LM head: pick_lm_tiling.)
+// Tiling of the residual products and of the row-major QKV projection (measured on MI355X):
+// 128 x 128 tiles for few rows (more tiles to spread over 256 CUs), the 8-wave 64-wide-k
+// tiling for QKV-sized fp32 outputs, 256 x 256 tiles (a third fewer operand bytes per flop,
+// two stages in flight) once there are enough rows, 128 x 256 otherwise.  (The LM head and
+// gate/up: pick_tiling.)
 int pick_variant(int epi, int M, int N, int K, int packed) {
   if (packed) {
     // measured on MI355X in the verify steps (272 - 4096 rows).  What sets these products'
@@ -1085,18 +1085,6 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     // products take 128 x 512 tiles (64 x 512 for the residual product with a short K
     // at ~520 rows, where 128-row tiles leave most of a last round empty); fewer rows take
     // 128 x 128 ones (and up to 288 rows most products run in gemm_rows_kernel).
-    if (epi == EPI_SWIGLU) {
-      // 288 x 256 tiles with the weights through LDS where their row padding and last
-      // round waste less: one workgroup a CU either way, a round costs its tile's area
-      // (520 rows: 112 us against 122).  Their offsets into the weights are 32 bits.
-      const long long cols = 2ll * N;
-      auto cost = [&](int tbm, int tbn) {
-        const long long tiles = (M + tbm - 1) / tbm * ((cols + tbn - 1) / tbn);
-        return (tiles + 255) / 256 * tbm * tbn;
-      };
-      if (cols * K < (1ll << 31) && cost(288, 256) < cost(128, 512)) return 12;
-      return 9;
-    }
     if (M <= 384) return 6;
     if (epi == EPI_RESID) return K < 8192 && M <= 640 ? 10 : 9;
     if (M >= 2048) return 5;
@@ -1104,7 +1092,7 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
   }
   if (M <= 384) return 1;
   if (epi == EPI_F32 && N <= 8192) return 2;
-  if (M >= (epi == EPI_SWIGLU ? 512 : 1024)) return 3;
+  if (M >= 1024) return 3;
   return 0;
 }
 
@@ -1147,88 +1135,120 @@ bool rows_ok(int epi, int M, int N, int K, int packed) {
   return M <= kFewRows;
 }
 
-// The LM head's tiling: the candidate with the smallest estimate.  A 64-wide k step takes a
-// workgroup alone on its CU `one` us and two of them `two` (-1: gemm_rows_kernel, for its
-// least row tile; `row` more per further 16 rows), and the last round of workgroups counts
-// whole; nothing goes faster than the weights' stream (`tbs` TB/s, less where fewer than 0.6
-// of the CUs pull it, and `again` of it more for each further row tile, whose panels the
-// L2s do not all share); the logits cost `store` us a MB.  Fitted to 1 .. 2048 rows of 4096
-// .. 152064 ids, width 2048 .. 8192 (6 to 8 % off a time); the pick is 1.4 % (packed) and
-// 0.4 % off the best candidate on average.  Whole thresholds on the rows, as the other products have, miss what the
-// vocabulary does to the rounds: packed at 96 rows of 16384 ids, width 4096, 128 x 512 tiles
-// (32 of them) take 98 us, 128 x 128 49; at 96 rows of 98304 ids 162 and 174.
-struct LmTiling {
+// The tiling of the LM head, and of gate/up beyond kFewRows: the candidate with the smallest
+// estimate.  A 64-wide k step takes a workgroup alone on its CU `one` us and two of them
+// `two` (-1: gemm_rows_kernel, for its least row tile; `row` more per further 16 rows), and
+// the last round of workgroups counts whole; nothing goes faster than the weights' stream
+// (`tbs` TB/s, less where fewer than 0.6 of the CUs pull it, and `again` of it more for each
+// further row tile, whose panels the L2s do not all share); the output costs `store` us a
+// MB.  Fitted to the LM head of 1 .. 2048 rows, 4096 .. 152064 ids and widths 2048 .. 8192
+// (6 to 8 % off a time) and to gate/up of 289 .. 2048 rows, 1024 x 2048 .. 8192 x 28672 (5 %
+// off).  The pick is 1.4 % (LM head, packed) and 0.4 % (the others) off the best candidate
+// on average.  Thresholds on the rows, as the other products have, miss what the columns do
+// to the rounds: packed LM head at 96 rows of 16384 ids, width 4096, 128 x 512 tiles (32 of
+// them) take 98 us, 128 x 128 49; at 96 rows of 98304 ids 162 and 174; row-major gate/up at
+// 1024 rows of 1024 x 2048, 256 x 256 tiles 33 and 128 x 128 30, of 4096 x 14336 215 and 223.
+struct TileRates {
   int var;
   float one, row, two, store, tbs, again;
 };
-constexpr LmTiling kLmPacked[] = {
+constexpr TileRates kLmPacked[] = {
     {-1, 0.50f, 0.02f, 0.96f, 0.41f, 6.24f, 0.f},
     {6, 0.64f, 0.f, 1.03f, 0.22f, 5.00f, 0.50f},
     {4, 0.92f, 0.f, 1.56f, 0.25f, 5.15f, 0.30f},
     {9, 1.36f, 0.f, 0.f, 0.31f, 5.30f, 0.20f},
     {12, 1.52f, 0.f, 0.f, 0.36f, 4.90f, 0.44f},
 };
-constexpr LmTiling kLmRows[] = {
+constexpr TileRates kLmRows[] = {
     {-1, 0.70f, 0.01f, 0.99f, 0.70f, 5.07f, 0.f},
     {1, 0.80f, 0.f, 1.09f, 0.31f, 4.53f, 0.40f},
     {0, 1.46f, 0.f, 1.85f, 0.29f, 3.89f, 0.20f},
     {3, 1.41f, 0.f, 0.f, 0.33f, 4.02f, 0.50f},
+};
+constexpr TileRates kSwigluPacked[] = {
+    {6, 0.69f, 0.f, 1.10f, 0.43f, 6.00f, 0.80f},
+    {4, 0.92f, 0.f, 1.52f, 0.58f, 6.20f, 0.48f},
+    {9, 1.42f, 0.f, 0.f, 0.55f, 6.46f, 0.47f},
+    {12, 1.55f, 0.f, 0.f, 0.69f, 3.81f, 0.72f},
+};
+constexpr TileRates kSwigluRows[] = {
+    {1, 0.82f, 0.f, 1.12f, 0.58f, 4.50f, 0.30f},
+    {0, 1.53f, 0.f, 1.87f, 0.33f, 8.87f, 1.08f},
+    {3, 1.49f, 0.f, 0.f, 0.58f, 4.31f, 0.84f},
 };
 // gemm_rows_kernel's LM head: beyond 48 row-major rows its panels leave LDS for one workgroup
 // a CU, whose logit stores nothing then overlaps (80 rows: 309 us against 221 with 128 x 128
 // tiles); packed, registers do from 81 rows.
 constexpr int kLmRowsPacked = 80, kLmRowsRows = 48;
 
-SplitPlan plan_lm(int var, int M, int N, int K, int cus, long long part_cap) {
+struct TileGrid {
+  int tbm, tbn, mt, nt;
+};
+TileGrid tile_grid(int var, int epi, int M, int N) {
   const GemmVariant v = kVariants[var];
-  const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
-  const int tiles = (M + tbm - 1) / tbm * ((N + tbn - 1) / tbn);
-  const SplitPlan sp = plan_split(M, N, K, v.kss, tbm, tbn, tiles, cus, v.occ, part_cap);
+  TileGrid g{v.wmn * v.wtm * 16, v.wnn * v.wtn * 16, 0, 0};
+  g.mt = (M + g.tbm - 1) / g.tbm;
+  g.nt = epi == EPI_SWIGLU ? (N + g.tbn / 2 - 1) / (g.tbn / 2) : (N + g.tbn - 1) / g.tbn;
+  return g;
+}
+SplitPlan plan_tiles(int var, int epi, int M, int N, int K, int cus, long long part_cap) {
+  const GemmVariant v = kVariants[var];
+  const TileGrid g = tile_grid(var, epi, M, N);
+  const SplitPlan sp =
+      plan_split(M, N, K, v.kss, g.tbm, g.tbn, g.mt * g.nt, cus, v.occ, part_cap);
   // the row maxima of sliced tiles are reduced by tbn / 4 lanes of one wave: wider tiles
   // stay whole (at most part of a last round idles)
-  return sp.tsplit > 1 && tbn / 4 > 64 ? SplitPlan{tiles, 1} : sp;
+  if (epi == EPI_F32_MAX && sp.tsplit > 1 && g.tbn / 4 > 64) return SplitPlan{g.mt * g.nt, 1};
+  return sp;
 }
 
-// -1: gemm_rows_kernel.
-int pick_lm_tiling(int M, int N, int K, int packed, int cus, long long part_cap) {
+// epi: EPI_F32_MAX or EPI_SWIGLU.  -1: gemm_rows_kernel.
+int pick_tiling(int epi, int M, int N, int K, int packed, int cus, long long part_cap) {
+  const long long cols = epi == EPI_SWIGLU ? 2ll * N : N;
+  const double weights_mb = (double)cols * K * 2e-6;
+  const double out_mb = (double)M * N * (epi == EPI_SWIGLU ? 2e-6 : 4e-6);
   double best = 1e30;
   int pick = 0;
-  auto estimate = [&](const LmTiling &t) {
-    const double mb = (double)N * K * 2e-6;   // the weights
-    double rounds, extra = 0.0;
+  auto round_us = [&](int wgs, double one, double two, int occ) {
+    if (occ == 1) return (wgs + cus - 1) / cus * one;
+    const int rest = wgs % (2 * cus);
+    return wgs / (2 * cus) * two + (rest == 0 ? 0.0 : rest <= cus ? one : two);
+  };
+  auto estimate = [&](const TileRates &t) {
+    double rounds, sums = 0.0;
     int mt = 1, wgs;
-    auto round_us = [&](int n, double one, double two, int occ) {
-      if (occ == 1) return (n + cus - 1) / cus * one;
-      const int rest = n % (2 * cus);
-      return n / (2 * cus) * two + (rest == 0 ? 0.0 : rest <= cus ? one : two);
-    };
     if (t.var < 0) {
       if (M > (packed ? kLmRowsPacked : kLmRowsRows) || K % 64 || N % 16) return;
-      const RowsPlan p = plan_rows(EPI_F32_MAX, M, N, K, cus, 0);
-      const double more = t.row * p.mb;   // (five row blocks: one workgroup as two)
+      const RowsPlan p = plan_rows(epi, M, N, K, cus, 0);
+      const double more = t.row * p.mb;   // (alone, five row blocks take half as long again)
       wgs = p.mt * p.nt;
-      rounds = round_us(wgs, more + (p.mb <= 3 ? t.one : 0.75), more + t.two, 2);
+      rounds = round_us(wgs, more + (p.mb <= 3 ? t.one : 1.5 * t.one), more + t.two, 2);
     } else {
       const GemmVariant v = kVariants[t.var];
-      const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
-      mt = (M + tbm - 1) / tbm;
-      if (v.pk == 3 && (long long)N * K >= 1ll << 31) return;   // (32-bit weight offsets)
-      const SplitPlan sp = plan_lm(t.var, M, N, K, cus, part_cap);
-      const int tiles = mt * ((N + tbn - 1) / tbn), rest = tiles - sp.full;
+      if (v.pk == 3 && cols * K >= 1ll << 31) return;   // (32-bit weight offsets)
+      const TileGrid g = tile_grid(t.var, epi, M, N);
+      const SplitPlan sp = plan_tiles(t.var, epi, M, N, K, cus, part_cap);
+      const int rest = g.mt * g.nt - sp.full;
+      mt = g.mt;
       wgs = sp.full + rest * sp.tsplit;
       rounds = round_us(sp.full, t.one, t.two, v.occ);
       if (sp.tsplit > 1) {
         rounds += round_us(rest * sp.tsplit, t.one, t.two, v.occ) / sp.tsplit;
-        extra = 4.0 + 1.6e-6 * rest * sp.tsplit * tbn * M / mt;   // the fp32 sums' round trip
+        sums = 4.0 + 1.6e-6 * rest * sp.tsplit * g.tbn * M / mt;   // fp32 sums' round trip
       }
     }
-    const double us = std::max(mb * (1.0 + t.again * (mt - 1)) / (t.tbs * std::min(1.0, 1.7 * wgs / cus)),
-                               K / 64 * rounds) +
-                      t.store * M * N * 4e-6 + extra;
+    const double stream =
+        weights_mb * (1.0 + t.again * (mt - 1)) / (t.tbs * std::min(1.0, 1.7 * wgs / cus));
+    const double us = std::max(stream, K / 64 * rounds) + t.store * out_mb + sums;
     if (us < best) { best = us; pick = t.var; }
   };
-  if (packed) for (const LmTiling &t : kLmPacked) estimate(t);
-  else for (const LmTiling &t : kLmRows) estimate(t);
+  if (epi == EPI_SWIGLU) {
+    if (packed) for (const TileRates &t : kSwigluPacked) estimate(t);
+    else for (const TileRates &t : kSwigluRows) estimate(t);
+  } else {
+    if (packed) for (const TileRates &t : kLmPacked) estimate(t);
+    else for (const TileRates &t : kLmRows) estimate(t);
+  }
   return pick;
 }
 
@@ -1274,14 +1294,10 @@ hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 
                                const TB *W, int M, int N, int K, f16 *out, float *outf,
                                float *part, long long part_cap, int cus, hipStream_t s,
                                int packed) {
-  if (var < 0) var = pick_variant(epi, M, N, K, packed);
-  if (var >= kNumVariants || (kVariants[var].pk != 0) != (packed != 0)) return hipErrorInvalidValue;
-  const GemmVariant v = kVariants[var];
-  const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
-  const int mt = (M + tbm - 1) / tbm;
-  const int nt = epi == EPI_SWIGLU ? (N + tbn / 2 - 1) / (tbn / 2) : (N + tbn - 1) / tbn;
+  if (var < 0 || var >= kNumVariants || (kVariants[var].pk != 0) != (packed != 0)) return hipErrorInvalidValue;
+  const auto [tbm, tbn, mt, nt] = tile_grid(var, epi, M, N);
   const int tiles = mt * nt;
-  SplitPlan sp = plan_split(M, N, K, v.kss, tbm, tbn, tiles, cus, v.occ, part_cap);
+  SplitPlan sp = plan_tiles(var, epi, M, N, K, cus, part_cap);
   if (splits_override == 1) sp = SplitPlan{tiles, 1};
   else if (splits_override > 1 &&
            (long long)tiles * splits_override * tbm * tbn <= part_cap)
@@ -1366,7 +1382,8 @@ hipError_t launch_gemm<bf16, f16>(int epi, const f16 *A, const bf16 *W, int M, i
                            plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0), aux.packed);
     return hipGetLastError();
   }
-  return launch_f16w_variant<bf16>(-1, 0, epi, A, W, M, N, K, out, outf, aux.part,
+  const int var = pick_tiling(epi, M, N, K, aux.packed, aux.cus, aux.part_cap);
+  return launch_f16w_variant<bf16>(var, 0, epi, A, W, M, N, K, out, outf, aux.part,
                                    aux.part_cap, aux.cus, s, aux.packed);
 }
 
@@ -1466,20 +1483,18 @@ template <>
 hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, int K,
                                      float *logits, float *tile_max, int *ntile,
                                      const GemmAux &aux, hipStream_t s) {
-  const int var = pick_lm_tiling(M, N, K, aux.packed, aux.cus, aux.part_cap);
+  const int var = pick_tiling(EPI_F32_MAX, M, N, K, aux.packed, aux.cus, aux.part_cap);
   if (var < 0) {
     const RowsPlan mp = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0);
     launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (f16 *)nullptr, logits, mp, aux.packed, tile_max);
     *ntile = mp.nt;
     return hipGetLastError();
   }
-  const GemmVariant v = kVariants[var];
-  const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
-  const int mt = (M + tbm - 1) / tbm, nt = (N + tbn - 1) / tbn;
-  launch_epi<EPI_F32_MAX, bf16>(var, s, A, W, M, N, K, nullptr, logits, aux.part, mt, nt,
-                                plan_lm(var, M, N, K, aux.cus, aux.part_cap), RopeOut<bf16>{},
-                                tile_max);
-  *ntile = nt;
+  const TileGrid g = tile_grid(var, EPI_F32_MAX, M, N);
+  launch_epi<EPI_F32_MAX, bf16>(
+      var, s, A, W, M, N, K, nullptr, logits, aux.part, g.mt, g.nt,
+      plan_tiles(var, EPI_F32_MAX, M, N, K, aux.cus, aux.part_cap), RopeOut<bf16>{}, tile_max);
+  *ntile = g.nt;
   return hipGetLastError();
 }
 

@@ -109,6 +109,18 @@ def test_tree_wide_tiles(B, depth, F, V):
     _check_tree(run, tol=2e-2)
 
 
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("B, depth, d, F", [
+    (5, 59, 1024, 4096), (9, 32, 256, 13376), (12, 31, 512, 8192), (12, 31, 2048, 4096),
+    (17, 31, 512, 8192)])
+def test_tree_gate_up_tilings(B, depth, d, F, packed):
+    """Gate/up beyond the few-row GEMM, 297 to 544 rows, at sizes whose least estimated time
+    belongs to each of its tilings (288 x 256 tiles: the test above), one of them with
+    k-slices; partial last row and column tiles."""
+    w = small_bf16(d=d, F=F, B=B, S=40, tree="chain", depth=depth, V=2000, L=1)
+    _check_tree(hz.run_tree(w, packed=packed), tol=2e-2)
+
+
 @pytest.mark.parametrize("B, depth, kw", [
     (1, 0, dict()), (2, 7, dict(d=64, F=64, H=1, Hkv=1, V=100)), (1, 16, dict(d=1024, F=2048)),
     (3, 20, dict(hd=128, H=2, Hkv=1, S=600)), (3, 48, dict(hd=128, H=4, Hkv=4, S=255, V=20004)),
@@ -343,7 +355,8 @@ def test_tail_split_rows(rows, V, kind):
     (1, 64, 64, False), (48, 4112, 512, False), (49, 4112, 512, True), (80, 50272, 256, False),
     (81, 50272, 256, False), (96, 4112, 4096, False), (96, 16400, 512, True),
     (129, 16400, 512, False), (160, 32016, 1024, True), (289, 8208, 2048, False),
-    (300, 32016, 256, False), (513, 16400, 1024, False), (577, 32016, 512, False)])
+    (272, 48016, 512, False), (288, 66000, 1024, False), (300, 32016, 256, False),
+    (513, 16400, 1024, False), (577, 32016, 512, False)])
 def test_lm_head_row_counts(rows, V, d, noalloc, packed):
     """The LM head's tilings, as its rows and vocabulary pick them: whole and sliced tiles of
     each size with a partial last row and column tile.  Logits against float64: a product of
