@@ -1126,11 +1126,14 @@ RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap, int es 
 // (8B / 1B shapes, us): gate/up at 138 rows 47 for 87 (packed) and 52 for 142 (row-major),
 // at 272 rows 25 for 31 (1B); beyond 288 rows the larger tiles are faster (packed, 384 rows:
 // 98 against 114).  The residual products keep it longer (down at 520 rows: 77 for 97
-// row-major), but for the packed 8B-class ones from 289 rows (432: 79 against 71).
+// row-major), up to widths whose weights need several rounds of its tiles a k-slice: packed
+// 32 Mi elements (8B-class, 432 rows: 79 against 71), row-major 64 Mi (us, against 128 x 256
+// and 256 x 256 tiles: 8192 x 8192, 512 rows 105 against 114; 5120 x 27648, 448 rows 242
+// against 184; 8192 x 28672, 289 rows 294 against 267).
 constexpr int kFewRows = 288, kSomeRows = 544;
 bool rows_ok(int epi, int M, int N, int K, int packed) {
   if (K % 64 != 0 || N % 16 != 0) return false;
-  if (epi == EPI_RESID && M <= kSomeRows && !(packed && (long long)N * K > (32 << 20)))
+  if (epi == EPI_RESID && M <= kSomeRows && (long long)N * K <= (packed ? 32ll : 64ll) << 20)
     return true;
   return M <= kFewRows;
 }

@@ -121,6 +121,14 @@ def test_tree_gate_up_tilings(B, depth, d, F, packed):
     _check_tree(hz.run_tree(w, packed=packed), tol=2e-2)
 
 
+@pytest.mark.parametrize("d, F", [(4096, 16384), (4096, 16448)])
+def test_tree_wide_residual(d, F):
+    """The row-major down projection of 297 rows at the widest weights that the few-row GEMM
+    takes beyond 288 rows and at the narrowest that it leaves to the larger tiles."""
+    w = small_bf16(d=d, F=F, B=9, S=40, tree="chain", depth=32, V=1000, L=1)
+    _check_tree(hz.run_tree(w), tol=2e-2)
+
+
 @pytest.mark.parametrize("B, depth, kw", [
     (1, 0, dict()), (2, 7, dict(d=64, F=64, H=1, Hkv=1, V=100)), (1, 16, dict(d=1024, F=2048)),
     (3, 20, dict(hd=128, H=2, Hkv=1, S=600)), (3, 48, dict(hd=128, H=4, Hkv=4, S=255, V=20004)),
