@@ -468,7 +468,9 @@ AS_DEVICE bool segment_pass_untied(const float *z, const float *q, int V, int sb
 template <typename TieBase>
 AS_DEVICE bool segment_pass(const float *z, const float *q, int V, int sb, int se, bool resid,
                             const Sel &sel, VTop &sm, TieBase tie_base, u64 *seg_p, u64 *seg_r) {
-  if (sel.c_p <= 1 && sel.c_k <= 1)
+  // (rows of fewer segments than the workgroup's 16-lane groups leave some of those idle: 2048
+  // rows of 1024 ids take 101 us in all this way and 106 that, of 8192 ids 138 and 134)
+  if (sel.c_p <= 1 && sel.c_k <= 1 && V >= NWV * 4 * SEG)
     return segment_pass_untied(z, q, V, sb, se, resid, sel, sm, seg_p, seg_r);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool badq = false;
@@ -1324,12 +1326,19 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
 
 namespace acespec {
 
-// Chunks of a row, 1: whole rows.  Six launches take about 45 us however small they are, a
-// whole row of 32000 ids 60, of 128256 ids 170, as long as each row has a CU to itself; the
-// rows' bytes take over from there (split against whole, us: 128256 ids, 16 rows 51 / 172,
-// 128 95 / 175, 512 253 / 297; 32000 ids, 128 rows 55 / 62, 200 rows 64 / 62).
-int vocab_chunks(int rows, int V, bool have_max) {
-  if (!have_max || rows < 1 || V < 16384 || rows > (V >= 48000 ? kVocabSplitRows : 128)) return 1;
+// Chunks of a row, 1: whole rows.  Six launches take about 43 us however small they are, a
+// whole row of 20000 ids 42, of 32000 ids 54, of 128256 ids 140, as long as each row has a
+// CU to itself; the rows' bytes take over from there, the sooner the shorter the row.  Split
+// against whole, us: 16384 ids, 1 row 41 / 37; 20000 ids, 17 rows 43 / 44, 48 rows 47 / 45;
+// 24000 ids, 17 rows 45 / 48, 128 rows 52 / 50; 32000 ids, 128 rows 54 / 58; 128256 ids, 17
+// rows 54 / 143.  From 48000 ids on, 512 rows with top_p below 1 (50272 ids 123 / 138, 128256
+// ids 249 / 312), 384 with top_p 1, whose threshold lies among few ids, so that whole rows
+// need one pass less (384 rows 97 / 92 and 172 / 173, 448 rows 111 / 93 and 204 / 178).
+// Beyond 512 rows there are not two chunks a row for the workgroups that the CUs hold.
+int vocab_chunks(int rows, int V, float top_p, bool have_max) {
+  const int most = V < 20000 ? 0 : V < 24000 ? 32 : V < 48000 ? 128
+                                     : top_p < 1.f ? kVocabSplitRows : 384;
+  if (!have_max || rows < 1 || rows > most) return 1;
   const int nseg = (V + SEG - 1) / SEG;
   int c = 1024 / rows;   // every CU holds four of the chunks' workgroups
   if (c > 32) c = 32;
@@ -1337,14 +1346,14 @@ int vocab_chunks(int rows, int V, bool have_max) {
   return c < 1 ? 1 : c;
 }
 size_t vocab_split_bytes(int rows, int V) {
-  const int c = vocab_chunks(rows, V, true);
+  const int c = vocab_chunks(rows, V, 0.f, true);   // (the most that any top_p takes)
   return c > 1 ? (size_t)rows * split_row_bytes(c, (V + SEG - 1) / SEG) : 0;
 }
 
 hipError_t launch_vocab(const VocabArgs &args, hipStream_t s) {
   if (args.V > SEGMAX * SEG || args.k > KMAX || args.k < 1) return hipErrorInvalidValue;
   VocabArgs a = args;
-  a.chunks = vocab_chunks(a.rows, a.V, a.tile_max != nullptr);
+  a.chunks = vocab_chunks(a.rows, a.V, a.top_p, a.tile_max != nullptr);
   const dim3 rows(a.rows), parts(a.rows * a.chunks), block(VT);
   if (a.chunks == 1 || !a.split || vocab_split_bytes(a.rows, a.V) > a.split_bytes) {
     hipLaunchKernelGGL(vocab_verify_kernel<false>, rows, block, 0, s, a);

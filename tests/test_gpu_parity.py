@@ -350,7 +350,7 @@ def test_tail_split_rows(rows, V, kind):
     (all but a few ids without mass)."""
     w = synth.get("8b-lmhead-tail").scaled(name="tail-split", d=128, V=V, rows=rows, chain_len=1,
                                           top_k=40, T={"cold": 0.03, "flat": 40.0}.get(kind, 0.8),
-                                          top_p=0.6)
+                                          top_p=1.0 if kind == "full" else 0.6)
     W = synth.make_weights(w, "cuda")
     if kind.startswith("ties"):
         n = int(kind[4:])
@@ -431,6 +431,17 @@ def test_tail_fp32_activations_past_4_gib():
     for r0 in (0, 131072 - 100, R - 400):
         want = hidden[r0:r0 + 400].double() @ lm.double().t()
         assert (outs["logits_out"][r0:r0 + 400].double() - want).abs().max() < 2e-4, r0
+
+
+@pytest.mark.parametrize("rows, V, kind", [
+    (32, 20000, "plain"), (33, 20000, "plain"), (128, 24000, "plain"), (129, 24000, "plain"),
+    (300, 96000, "plain"), (384, 48000, "full"), (385, 48000, "full"), (40, 7936, "plain"),
+    (40, 8192, "plain"), (40, 7936, "ties8"), (40, 512, "flat")])
+def test_tail_row_rules(rows, V, kind):
+    """As above, at the edges of the rule by which rows are split (their number by the length
+    of a row, where there are many by top_p), at two and three chunks a row, and where the last
+    pass changes its form (8192 ids)."""
+    test_tail_split_rows(rows, V, kind)
 
 
 def _bin_edge(M, T, b):
