@@ -1042,14 +1042,20 @@ hipError_t launch_attention<bf16>(const f16 *q, const bf16 *ck, const bf16 *cv,
   const bool t32 = all_tiles > 16;
   const int nqg = t32 ? (QR + 271) / 272 : 1;
   const int rpg = (QR + nqg - 1) / nqg;
-  // Key splits: as many as the CUs hold at once (6 sessions of 8 kv heads: six splits, 288
-  // workgroups and so two rounds, took 29.2 us, five 24.6), of at least 2 chunks (a single
-  // session of 1500 slots, with the combine: 16.2 us against 17.3 at 4 chunks).
+  // Key splits: as many as the CUs hold at once, rounded down, for a second round of a few
+  // workgroups costs what the first does (6 sessions of 8 kv heads: six splits, 288
+  // workgroups, took 29.2 us, five 24.6; where the items do not divide the CUs some idle).
+  // A split is at least 4 chunks, as the merge's launch and its fp32 partials cost about as
+  // much as three (16 sessions of 8 kv heads, 300 slots, two splits 27.3 us, whole 21.0),
+  // but 2 for up to 32 items, whose few partials cost little, if the chunks' query tiles add
+  // up to some work (one session of 1500 slots: 16.2 us against 17.3 at 4 chunks; 65 rows of
+  // 8 query heads over 300 slots: 26 against 33 whole).
   const int slots = cus;
   const int items = B * Hkv * nqg;
   const int nchunks = capacity / KC;
   int nsplit = slots / items;
-  nsplit = nsplit < nchunks / 2 ? nsplit : nchunks / 2;
+  const int least = items <= 32 && nchunks * all_tiles >= 48 ? 2 : 4;
+  nsplit = nsplit < nchunks / least ? nsplit : nchunks / least;
   if (nsplit < 1) nsplit = 1;
   while (nsplit > 1 && (long long)B * Hkv * nsplit * QR * hd > part_capacity) --nsplit;
   *nsplit_used = nsplit;

@@ -121,6 +121,17 @@ def test_tree_gate_up_tilings(B, depth, d, F, packed):
     _check_tree(hz.run_tree(w, packed=packed), tol=2e-2)
 
 
+@pytest.mark.parametrize("B, H, Hkv, S", [
+    (1, 8, 8, 400), (1, 32, 8, 250), (2, 16, 8, 1520), (3, 8, 8, 3050), (3, 8, 8, 1100),
+    (16, 8, 8, 300), (17, 8, 8, 600)])
+def test_tree_key_splits(B, H, Hkv, S):
+    """Attention over prefixes on either side of the rule that splits their keys: a few
+    sessions in splits of 2 chunks or of 4, short prefixes that stay whole, and batches that
+    leave no split or do not divide the CUs."""
+    w = small_bf16(B=B, H=H, Hkv=Hkv, hd=128, S=S, ragged=False, V=1000, L=1)
+    _check_tree(hz.run_tree(w), tol=2e-2)
+
+
 @pytest.mark.parametrize("d, F", [(4096, 16384), (4096, 16448)])
 def test_tree_wide_residual(d, F):
     """The row-major down projection of 297 rows at the widest weights that the few-row GEMM
