@@ -212,7 +212,7 @@ int verify_tree_impl(acespec_ctx *ctx, const acespec_weights *w, const acespec_k
   va.logits = logits;
   va.q = draft_q;
   va.q_scalar = q_scalar;
-  va.tile_max = ntile ? ctx->tile_max : nullptr;
+  va.tile_max = ctx->tile_max;
   va.ntile = ntile;
   va.cand = ctx->cand;
   va.cand_cap = kCandCap;
@@ -280,7 +280,7 @@ int verify_tail_run(acespec_ctx *ctx, const acespec_model_desc &d, const TailWor
   va.logits = logits;
   va.q = draft_q;
   va.q_scalar = nullptr;
-  va.tile_max = ntile ? ws.tile_max : nullptr;
+  va.tile_max = ws.tile_max;
   va.ntile = ntile;
   va.cand = ws.cand;
   va.cand_cap = ws.cand_cap;

@@ -290,14 +290,6 @@ hipError_t launch_gemm_resid_norm(const TA *A, const TW *W, int M, int N, int K,
                                   const TW *gain, typename ActOf<TW>::type *out, float eps,
                                   const GemmAux &aux, hipStream_t s);
 
-// The fp16-activation MFMA GEMM (weights TB = bf16, widened to fp16 in registers) in the
-// tiling var, with a split count (splits_override > 0) or the planned one.
-template <typename TB>
-hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 *A,
-                               const TB *W, int M, int N, int K, f16 *out, float *outf,
-                               float *part, long long part_cap, int cus, hipStream_t s,
-                               int packed = 0);
-
 // Packs a row-major bf16 weight matrix [rows, K] (rows % 16 == 0, K % 32 == 0) into the
 // fp16 MFMA-fragment order the packed GEMM path reads (same byte size).
 hipError_t launch_pack_weights(const bf16 *W, f16 *P, int rows, int K, hipStream_t s);
@@ -317,7 +309,7 @@ struct VocabArgs {
   const float *logits;      // [rows, V]
   const float *q;           // [rows, V] dense draft distributions (NULL in scalar mode)
   const float *q_scalar;    // [rows] q-hat of each row's own token, or NULL (dense mode)
-  const float *tile_max;    // [rows, ntile] row maxima over column tiles, or NULL
+  const float *tile_max;    // [rows, ntile] row maxima over column tiles
   int ntile;
   uint32_t *cand;           // [rows, cand_cap] scratch for threshold-bin candidates, or NULL
   int cand_cap;

@@ -962,6 +962,7 @@ using acespec::EPI_RESID;
 using acespec::EPI_SWIGLU;
 using acespec::EPI_F32;
 using acespec::EPI_F32_MAX;
+using acespec::EPI_QKV_ROPE;
 
 // Tilings: {waves M, waves N, wave tile M / 16, wave tile N / 16, stages, WGs per CU,
 // k per stage, weight layout}.  Measured on MI355X against the verify-step shapes.  Tried
@@ -969,8 +970,7 @@ using acespec::EPI_F32_MAX;
 // (one issuing 32 x 32 MFMAs while the other loads), deeper rings (5-8 stages) at one
 // workgroup per CU, with 64 x 64 wave tiles or 128 x 512 block tiles (with packed weights
 // 128 x 512 tiles are the fastest), 128 x 128 tiles with 64-wide k stages, fp16 weights
-// (which only removes the in-register widening, worth 3-8 %), and weights and
-// activations pre-packed into 1 KB tile blocks (contiguous DMA; 2-9 %), 256 x 128 tiles,
+// (which only removes the in-register widening, worth 3-8 %), 256 x 128 tiles,
 // and 256 x 256 tiles on 32 x 32 MFMAs with one wave per SIMD (128 x 128 wave tiles: the
 // single wave cannot cover the barrier and DMA waits).
 struct GemmVariant {
@@ -983,16 +983,24 @@ constexpr GemmVariant kVariants[] = {
     {2, 4, 8, 4, 4, 1, 32, 0},  // 3: 256 x 256, 8 waves of 128 x 64, 128 KB LDS, 1 WG per CU
     // packed weights (registers fed straight from the fragment-ordered copy):
     {1, 4, 8, 4, 4, 2, 32, 1},  // 4: 128 x 256, 4 waves of 128 x 64, 32 KB ring, 2 WGs per CU
-    {2, 4, 8, 4, 4, 1, 32, 1},  // 5: 256 x 256, 8 waves of 128 x 64, 64 KB ring, 1 WG per CU
-    {2, 2, 4, 4, 4, 2, 32, 1},  // 6: 128 x 128, 4 waves of 64 x 64, 32 KB ring, 2 WGs per CU
-    {1, 4, 8, 4, 4, 1, 64, 2},  // 7: 128 x 256, two groups of 4 waves of 128 x 64 splitting k
-    {2, 2, 4, 4, 4, 1, 64, 2},  // 8: 128 x 128, two groups of 4 waves of 64 x 64 splitting k
-    {1, 8, 8, 4, 4, 1, 32, 1},  // 9: 128 x 512, 8 waves of 128 x 64, 32 KB ring, 1 WG per CU
-    {1, 8, 4, 4, 4, 1, 32, 1},  // 10: 64 x 512, 8 waves of 64 x 64, 16 KB ring, 1 WG per CU
-    {1, 4, 7, 4, 4, 1, 64, 2},  // 11: 112 x 256, two groups of 4 waves of 112 x 64 splitting k
-    {2, 4, 9, 4, 4, 1, 32, 3},  // 12: 288 x 256, 8 waves of 144 x 64, weights through LDS, 136 KB
+    {2, 2, 4, 4, 4, 2, 32, 1},  // 5: 128 x 128, 4 waves of 64 x 64, 32 KB ring, 2 WGs per CU
+    {2, 2, 4, 4, 4, 1, 64, 2},  // 6: 128 x 128, two groups of 4 waves of 64 x 64 splitting k
+    {1, 8, 8, 4, 4, 1, 32, 1},  // 7: 128 x 512, 8 waves of 128 x 64, 32 KB ring, 1 WG per CU
+    {1, 8, 4, 4, 4, 1, 32, 1},  // 8: 64 x 512, 8 waves of 64 x 64, 16 KB ring, 1 WG per CU
+    {1, 4, 7, 4, 4, 1, 64, 2},  // 9: 112 x 256, two groups of 4 waves of 112 x 64 splitting k
+    {2, 4, 9, 4, 4, 1, 32, 3},  // 10: 288 x 256, 8 waves of 144 x 64, weights through LDS, 136 KB
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
+
+// The tilings that a product is given by the rules below: only these are compiled for it.
+constexpr bool reaches(int epi, int var) {
+  switch (epi) {
+    case EPI_QKV_ROPE: return var <= 6 || var == 9;
+    case EPI_F32: return var <= 5;                        // (QKV that the epilogue cannot take)
+    case EPI_RESID: return var <= 1 || var == 3 || var == 5 || var == 7 || var == 8;
+    default: return var <= 1 || (var >= 3 && var <= 5) || var == 7 || var == 10;
+  }
+}
 
 // Work split of a product: `full` whole tiles, then `tsplit` k-slices of each of the
 // remaining tiles.  With at least one round of whole tiles, only the tiles of the last,
@@ -1054,21 +1062,23 @@ void launch_variant(hipStream_t s, const f16 *A, const TB *W, int M, int N, int 
 }
 
 template <int EPI, typename TB>
-void launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N, int K,
-                f16 *out, float *outf, float *part, int mt, int nt, SplitPlan sp,
-                const acespec::RopeOut<TB> &ro = acespec::RopeOut<TB>{},
-                float *tmax = nullptr) {
+hipError_t launch_epi(int var, hipStream_t s, const f16 *A, const TB *W, int M, int N, int K,
+                      f16 *out, float *outf, float *part, int mt, int nt, SplitPlan sp,
+                      const acespec::RopeOut<TB> &ro = acespec::RopeOut<TB>{},
+                      float *tmax = nullptr) {
   switch (var) {
 #define CASE(V)                                                                             \
   case V:                                                                                   \
-    if constexpr (kVariants[V].pk != 2 || EPI == acespec::EPI_QKV_ROPE)                     \
+    if constexpr (reaches(EPI, V)) {                                                        \
       launch_variant<EPI, V, TB>(s, A, W, M, N, K, out, outf, part, mt, nt, sp, ro, tmax);  \
+      return hipGetLastError();                                                             \
+    }                                                                                       \
     break;
     CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10)
-    CASE(11) CASE(12)
 #undef CASE
     default: break;
   }
+  return hipErrorInvalidValue;
 }
 
 // Tiling of the residual products and of the row-major QKV projection (measured on MI355X):
@@ -1085,10 +1095,8 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     // products take 128 x 512 tiles (64 x 512 for the residual product with a short K
     // at ~520 rows, where 128-row tiles leave most of a last round empty); fewer rows take
     // 128 x 128 ones (and up to 288 rows most products run in gemm_rows_kernel).
-    if (M <= 384) return 6;
-    if (epi == EPI_RESID) return K < 8192 && M <= 640 ? 10 : 9;
-    if (M >= 2048) return 5;
-    return 4;
+    if (M <= 384) return 5;
+    return K < 8192 && M <= 640 ? 8 : 7;
   }
   if (M <= 384) return 1;
   if (epi == EPI_F32 && N <= 8192) return 2;
@@ -1157,10 +1165,10 @@ struct TileRates {
 };
 constexpr TileRates kLmPacked[] = {
     {-1, 0.50f, 0.02f, 0.96f, 0.41f, 6.24f, 0.f},
-    {6, 0.64f, 0.f, 1.03f, 0.22f, 5.00f, 0.50f},
+    {5, 0.64f, 0.f, 1.03f, 0.22f, 5.00f, 0.50f},
     {4, 0.92f, 0.f, 1.56f, 0.25f, 5.15f, 0.30f},
-    {9, 1.36f, 0.f, 0.f, 0.31f, 5.30f, 0.20f},
-    {12, 1.52f, 0.f, 0.f, 0.36f, 4.90f, 0.44f},
+    {7, 1.36f, 0.f, 0.f, 0.31f, 5.30f, 0.20f},
+    {10, 1.52f, 0.f, 0.f, 0.36f, 4.90f, 0.44f},
 };
 constexpr TileRates kLmRows[] = {
     {-1, 0.70f, 0.01f, 0.99f, 0.70f, 5.07f, 0.f},
@@ -1169,10 +1177,10 @@ constexpr TileRates kLmRows[] = {
     {3, 1.41f, 0.f, 0.f, 0.33f, 4.02f, 0.50f},
 };
 constexpr TileRates kSwigluPacked[] = {
-    {6, 0.69f, 0.f, 1.10f, 0.43f, 6.00f, 0.80f},
+    {5, 0.69f, 0.f, 1.10f, 0.43f, 6.00f, 0.80f},
     {4, 0.92f, 0.f, 1.52f, 0.58f, 6.20f, 0.48f},
-    {9, 1.42f, 0.f, 0.f, 0.55f, 6.46f, 0.47f},
-    {12, 1.55f, 0.f, 0.f, 0.69f, 3.81f, 0.72f},
+    {7, 1.42f, 0.f, 0.f, 0.55f, 6.46f, 0.47f},
+    {10, 1.55f, 0.f, 0.f, 0.69f, 3.81f, 0.72f},
 };
 constexpr TileRates kSwigluRows[] = {
     {1, 0.82f, 0.f, 1.12f, 0.58f, 4.50f, 0.30f},
@@ -1256,21 +1264,31 @@ int pick_tiling(int epi, int M, int N, int K, int packed, int cus, long long par
 }
 
 template <int EPI, typename TA, typename TW>
-void launch_rows(hipStream_t s, const TA *A, const TW *W, int M, int N, int K, TA *out,
-                 float *outf, const RowsPlan &p, int packed, float *tmax = nullptr) {
-  // two workgroups a CU where the LM head's many tiles pass through it
-  constexpr int NROW = EPI == EPI_F32_MAX ? 3 : 4;
+hipError_t launch_rows(hipStream_t s, const TA *A, const TW *W, int M, int N, int K, TA *out,
+                       float *outf, const RowsPlan &p, int packed, float *tmax = nullptr) {
+  // (the 16-bit LM head's row blocks; its many tiles: row-major, two workgroups a CU)
+  constexpr bool LM = EPI == EPI_F32_MAX && sizeof(TA) == 2;
+  constexpr int MAXP = LM ? kLmRowsPacked / 16 : 9, MAXR = LM ? kLmRowsRows / 16 : 9;
 #define ROWS(MB)                                                                             \
   case MB:                                                                                   \
-    if constexpr (sizeof(TA) == 4)                                                           \
+    if constexpr (sizeof(TA) == 4) {                                                         \
       hipLaunchKernelGGL((gemm_rows_kernel<EPI, float, 0, MB, 4>), grid, dim3(512), 0, s, A,   \
                          W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                    \
-    else if (packed)                                                                         \
-      hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 1, MB, 5>), grid, dim3(512), 0, s, A, W,  \
-                         M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                       \
-    else                                                                                     \
-      hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 0, MB, MB <= 5 ? NROW : 4>), grid,        \
-                         dim3(512), 0, s, A, W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax); \
+      return hipGetLastError();                                                              \
+    } else {                                                                                 \
+      if constexpr (MB <= MAXP)                                                              \
+        if (packed) {                                                                        \
+          hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 1, MB, 5>), grid, dim3(512), 0, s, A, \
+                             W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);                \
+          return hipGetLastError();                                                          \
+        }                                                                                    \
+      if constexpr (MB <= MAXR)                                                              \
+        if (!packed) {                                                                       \
+          hipLaunchKernelGGL((gemm_rows_kernel<EPI, f16, 0, MB, LM ? 3 : 4>), grid, dim3(512), \
+                             0, s, A, W, M, N, K, out, outf, p.mt, p.nt, p.nsl, tmax);       \
+          return hipGetLastError();                                                          \
+        }                                                                                    \
+    }                                                                                        \
     break
   const dim3 grid(p.mt * p.nt * p.nsl);
   switch (p.mb) {
@@ -1278,6 +1296,7 @@ void launch_rows(hipStream_t s, const TA *A, const TW *W, int M, int N, int K, T
     default: break;
   }
 #undef ROWS
+  return hipErrorInvalidValue;
 }
 
 template <typename TW>
@@ -1292,25 +1311,23 @@ void launch_rows_resid_norm(hipStream_t s, const float *part, float *x, const TW
 
 namespace acespec {
 
+// A product in the tiling var with its planned k-slices.
 template <typename TB>
-hipError_t launch_f16w_variant(int var, int splits_override, int epi, const f16 *A,
-                               const TB *W, int M, int N, int K, f16 *out, float *outf,
-                               float *part, long long part_cap, int cus, hipStream_t s,
-                               int packed) {
+hipError_t launch_f16w_variant(int var, int epi, const f16 *A, const TB *W, int M, int N, int K,
+                               f16 *out, float *outf, float *part, long long part_cap, int cus,
+                               hipStream_t s, int packed) {
   if (var < 0 || var >= kNumVariants || (kVariants[var].pk != 0) != (packed != 0)) return hipErrorInvalidValue;
-  const auto [tbm, tbn, mt, nt] = tile_grid(var, epi, M, N);
-  const int tiles = mt * nt;
-  SplitPlan sp = plan_tiles(var, epi, M, N, K, cus, part_cap);
-  if (splits_override == 1) sp = SplitPlan{tiles, 1};
-  else if (splits_override > 1 &&
-           (long long)tiles * splits_override * tbm * tbn <= part_cap)
-    sp = SplitPlan{0, splits_override};
+  const TileGrid g = tile_grid(var, epi, M, N);
+  const SplitPlan sp = plan_tiles(var, epi, M, N, K, cus, part_cap);
   switch (epi) {
-    case EPI_RESID: launch_epi<EPI_RESID, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp); break;
-    case EPI_SWIGLU: launch_epi<EPI_SWIGLU, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp); break;
-    default: launch_epi<EPI_F32, TB>(var, s, A, W, M, N, K, out, outf, part, mt, nt, sp);
+    case EPI_RESID:
+      return launch_epi<EPI_RESID, TB>(var, s, A, W, M, N, K, out, outf, part, g.mt, g.nt, sp);
+    case EPI_SWIGLU:
+      return launch_epi<EPI_SWIGLU, TB>(var, s, A, W, M, N, K, out, outf, part, g.mt, g.nt, sp);
+    case EPI_F32:
+      return launch_epi<EPI_F32, TB>(var, s, A, W, M, N, K, out, outf, part, g.mt, g.nt, sp);
+    default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <int V, typename TB>
@@ -1329,7 +1346,9 @@ hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M,
   if (rows_ok(EPI_RESID, M, N, K, aux.packed) && N <= 8 * 4 * 256 &&
       (long long)M * N <= aux.part_cap) {
     const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
-    launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, aux.part, mp, aux.packed);
+    const hipError_t e =
+        launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, aux.part, mp, aux.packed);
+    if (e != hipSuccess) return e;
     launch_rows_resid_norm(s, aux.part, x, gain, out, M, N, mp.nsl, eps);
     return hipGetLastError();
   }
@@ -1340,7 +1359,7 @@ hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M,
   const SplitPlan sp =
       plan_split(M, N, K, v.kss, tbm, tbn, mt * nt, aux.cus, v.occ, aux.part_cap);
   if (sp.full != 0 || sp.tsplit < 2 || N % tbn != 0 || N > 8 * 4 * 256) {
-    hipError_t e = launch_f16w_variant<bf16>(var, 0, EPI_RESID, A, W, M, N, K, nullptr, x,
+    hipError_t e = launch_f16w_variant<bf16>(var, EPI_RESID, A, W, M, N, K, nullptr, x,
                                              aux.part, aux.part_cap, aux.cus, s, aux.packed);
     if (e != hipSuccess) return e;
     return launch_rmsnorm<bf16, float>(x, gain, out, M, N, eps, s);
@@ -1358,16 +1377,12 @@ hipError_t launch_gemm_resid_norm<bf16, f16>(const f16 *A, const bf16 *W, int M,
     launch_resid_norm_fixup<VV, bf16>(s, aux.part, x, gain, out, M, N, mt, sp.tsplit, eps); \
     break;                                                                                  \
   }
-    CASE(0) CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(9) CASE(10)
+    CASE(0) CASE(1) CASE(3) CASE(5) CASE(7) CASE(8)
 #undef CASE
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
-
-template hipError_t launch_f16w_variant<bf16>(int, int, int, const f16 *, const bf16 *, int, int,
-                                              int, f16 *, float *, float *, long long, int,
-                                              hipStream_t, int);
 
 hipError_t launch_pack_weights(const bf16 *W, f16 *P, int rows, int K, hipStream_t s) {
   if (rows <= 0 || K <= 0 || rows % 16 != 0 || K % 32 != 0) return hipErrorInvalidValue;
@@ -1380,13 +1395,12 @@ hipError_t launch_pack_weights(const bf16 *W, f16 *P, int rows, int K, hipStream
 template <>
 hipError_t launch_gemm<bf16, f16>(int epi, const f16 *A, const bf16 *W, int M, int N, int K,
                                   f16 *out, float *outf, const GemmAux &aux, hipStream_t s) {
-  if (epi == EPI_SWIGLU && rows_ok(epi, M, N, K, aux.packed)) {
-    launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, nullptr,
-                           plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0), aux.packed);
-    return hipGetLastError();
-  }
+  if (epi != EPI_SWIGLU) return hipErrorInvalidValue;
+  if (rows_ok(epi, M, N, K, aux.packed))
+    return launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, nullptr,
+                                   plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0), aux.packed);
   const int var = pick_tiling(epi, M, N, K, aux.packed, aux.cus, aux.part_cap);
-  return launch_f16w_variant<bf16>(var, 0, epi, A, W, M, N, K, out, outf, aux.part,
+  return launch_f16w_variant<bf16>(var, epi, A, W, M, N, K, out, outf, aux.part,
                                    aux.part_cap, aux.cus, s, aux.packed);
 }
 
@@ -1394,13 +1408,10 @@ template <>
 hipError_t launch_gemm<float, float>(int epi, const float *A, const float *W, int M, int N,
                                      int K, float *out, float *outf, const GemmAux &aux,
                                      hipStream_t s) {
-  RowsPlan p = plan_rows(EPI_RESID, M, N, K, aux.cus, 0, 4);   // (one slice)
-  if (epi == EPI_SWIGLU)
-    launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, outf,
-                            plan_rows(EPI_SWIGLU, M, N, K, aux.cus, 0, 4), 0);
-  else if (epi == EPI_RESID) launch_rows<EPI_RESID>(s, A, W, M, N, K, out, outf, p, 0);
-  else launch_rows<EPI_F32>(s, A, W, M, N, K, out, outf, p, 0);
-  return hipGetLastError();
+  const RowsPlan p = plan_rows(epi, M, N, K, aux.cus, 0, 4);   // (one slice)
+  if (epi == EPI_SWIGLU) return launch_rows<EPI_SWIGLU>(s, A, W, M, N, K, out, outf, p, 0);
+  if (epi == EPI_RESID) return launch_rows<EPI_RESID>(s, A, W, M, N, K, out, outf, p, 0);
+  return hipErrorInvalidValue;
 }
 
 template <>
@@ -1409,7 +1420,8 @@ hipError_t launch_gemm_resid_norm<float, float>(const float *A, const float *W, 
                                                 float eps, const GemmAux &aux, hipStream_t s) {
   if (N <= 8192 && (long long)M * N <= aux.part_cap) {
     const RowsPlan p = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap, 4);
-    launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, aux.part, p, 0);
+    const hipError_t e = launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, aux.part, p, 0);
+    if (e != hipSuccess) return e;
     launch_rows_resid_norm(s, aux.part, x, gain, out, M, N, p.nsl, eps);
     return hipGetLastError();
   }
@@ -1429,8 +1441,8 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
   if (rows_ok(EPI_F32, M, N, K, aux.packed)) {
     const RowsPlan mp = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap);
     float *dst = mp.nsl > 1 ? aux.part : qkv;
-    launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, dst, mp, aux.packed);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e =
+        launch_rows<EPI_F32>(s, A, W, M, N, K, (f16 *)nullptr, dst, mp, aux.packed);
     if (e != hipSuccess) return e;
     return launch_rope_kv<bf16>(dst, mp.nsl, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv,
                                 ro.hd, ro.capacity, ro.rot, s);
@@ -1440,28 +1452,24 @@ hipError_t launch_qkv_rope<bf16, f16>(const f16 *A, const bf16 *W, int M, int N,
     // with about one tile a CU), RoPE and cache write in the epilogue: 112 x 256 tiles from
     // ~1k rows (1088 rows: 240 tiles for 256 CUs and 32 padding rows, against 216 tiles and
     // 64 rows at 128 x 256), 128 x 128 below
-    const int gv = M >= 1024 ? 11 : 8;
+    const int gv = M >= 1024 ? 9 : 6;
     const GemmVariant g = kVariants[gv];
     const int mt = (M + g.wtm * 16 * g.wmn - 1) / (g.wtm * 16 * g.wmn);
     const int nt = (N + g.wtn * 16 * g.wnn - 1) / (g.wtn * 16 * g.wnn);
-    if (4 * mt * nt >= 3 * aux.cus) {
-      launch_epi<EPI_QKV_ROPE, bf16>(gv, s, A, W, M, N, K, nullptr, nullptr, aux.part, mt, nt,
-                                     SplitPlan{mt * nt, 1}, ro);
-      return hipGetLastError();
-    }
+    if (4 * mt * nt >= 3 * aux.cus)
+      return launch_epi<EPI_QKV_ROPE, bf16>(gv, s, A, W, M, N, K, nullptr, nullptr, aux.part, mt,
+                                            nt, SplitPlan{mt * nt, 1}, ro);
   }
-  const int var = aux.packed ? (M <= 384 ? 6 : 4) : pick_variant(EPI_F32, M, N, K, 0);
+  const int var = aux.packed ? (M <= 384 ? 5 : 4) : pick_variant(EPI_F32, M, N, K, 0);
   const GemmVariant v = kVariants[var];
   const int tbm = v.wmn * v.wtm * 16, tbn = v.wnn * v.wtn * 16;
   const int mt = (M + tbm - 1) / tbm, nt = (N + tbn - 1) / tbn;
   SplitPlan sp = plan_split(M, N, K, v.kss, tbm, tbn, mt * nt, aux.cus, v.occ, aux.part_cap);
   if (aux.packed && 4 * mt * nt >= 3 * aux.cus) sp = SplitPlan{mt * nt, 1};
-  if (sp.tsplit == 1 && tbn % ro.hd == 0 && fusable) {
-    launch_epi<EPI_QKV_ROPE, bf16>(var, s, A, W, M, N, K, nullptr, nullptr, aux.part, mt, nt,
-                                   sp, ro);
-    return hipGetLastError();
-  }
-  hipError_t e = launch_f16w_variant<bf16>(var, 0, EPI_F32, A, W, M, N, K, nullptr, qkv,
+  if (sp.tsplit == 1 && tbn % ro.hd == 0 && fusable)
+    return launch_epi<EPI_QKV_ROPE, bf16>(var, s, A, W, M, N, K, nullptr, nullptr, aux.part, mt,
+                                          nt, sp, ro);
+  const hipError_t e = launch_f16w_variant<bf16>(var, EPI_F32, A, W, M, N, K, nullptr, qkv,
                                            aux.part, aux.part_cap, aux.cus, s, aux.packed);
   if (e != hipSuccess) return e;
   return launch_rope_kv<bf16>(qkv, 1, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv, ro.hd,
@@ -1475,8 +1483,7 @@ hipError_t launch_qkv_rope<float, float>(const float *A, const float *W, int M, 
                                          hipStream_t s) {
   const RowsPlan p = plan_rows(EPI_F32, M, N, K, aux.cus, aux.part_cap, 4);
   float *dst = p.nsl > 1 ? aux.part : qkv;
-  launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, dst, p, 0);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = launch_rows<EPI_F32>(s, A, W, M, N, K, (float *)nullptr, dst, p, 0);
   if (e != hipSuccess) return e;
   return launch_rope_kv<float>(dst, p.nsl, ro.q, meta, ro.ck, ro.cv, B, ro.n1, ro.H, ro.Hkv,
                                ro.hd, ro.capacity, ro.rot, s);
@@ -1489,16 +1496,15 @@ hipError_t launch_lm_head<bf16, f16>(const f16 *A, const bf16 *W, int M, int N, 
   const int var = pick_tiling(EPI_F32_MAX, M, N, K, aux.packed, aux.cus, aux.part_cap);
   if (var < 0) {
     const RowsPlan mp = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0);
-    launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (f16 *)nullptr, logits, mp, aux.packed, tile_max);
     *ntile = mp.nt;
-    return hipGetLastError();
+    return launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (f16 *)nullptr, logits, mp, aux.packed,
+                                    tile_max);
   }
   const TileGrid g = tile_grid(var, EPI_F32_MAX, M, N);
-  launch_epi<EPI_F32_MAX, bf16>(
+  *ntile = g.nt;
+  return launch_epi<EPI_F32_MAX, bf16>(
       var, s, A, W, M, N, K, nullptr, logits, aux.part, g.mt, g.nt,
       plan_tiles(var, EPI_F32_MAX, M, N, K, aux.cus, aux.part_cap), RopeOut<bf16>{}, tile_max);
-  *ntile = g.nt;
-  return hipGetLastError();
 }
 
 template <>
@@ -1506,9 +1512,8 @@ hipError_t launch_lm_head<float, float>(const float *A, const float *W, int M, i
                                         float *logits, float *tile_max, int *ntile,
                                         const GemmAux &aux, hipStream_t s) {
   const RowsPlan p = plan_rows(EPI_F32_MAX, M, N, K, aux.cus, 0, 4);
-  launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (float *)nullptr, logits, p, 0, tile_max);
   *ntile = p.nt;
-  return hipGetLastError();
+  return launch_rows<EPI_F32_MAX>(s, A, W, M, N, K, (float *)nullptr, logits, p, 0, tile_max);
 }
 
 }  // namespace acespec

@@ -24,7 +24,8 @@
 // re-read and scanned across a wavefront.
 // Occupancy: 512 threads, 51 KB of LDS (the histograms of each pass and the segment
 // tables share storage; the refinement levels are sized to fit under pass 1's) and at most
-// 80 VGPRs per row, so three rows are in flight per CU and their scans and selections
+// 80 VGPRs per row (ten values spill: thread constants, reloaded between the passes and
+// three times a step of the last one), so three rows are in flight per CU and their scans and selections
 // overlap each other's passes over memory (two rows a CU give about 1.45x the throughput
 // of one, three about 10 % more than two); the row passes keep the next step's loads in
 // flight while processing the current one.
@@ -146,7 +147,7 @@ AS_DEVICE float block_max(float v, VScan &sm) {
 // Descending radix step: bins b = nb-1 .. 0 hold (count, mass).  Finds the bin where the
 // running mass from the top first reaches `target` (mass mode) or where the running
 // count first reaches `target` (count mode); returns the bin and the amount strictly
-// above it.  nb is 4096, 2048 or 512.
+// above it.  nb is 4096, 2048, 1024 or 512.
 template <bool MASS>
 AS_DEVICE void select_bin(VScan &sm, const uint32_t *cnt, const u64 *mass, int nb, u64 target,
                           u64 base, int &sel, u64 &above) {
@@ -319,8 +320,7 @@ AS_DEVICE int find_segment(const u64 *excl, int nseg, u64 target) {
 // before any is used: one load in flight per thread leaves the passes bound by memory
 // latency rather than bandwidth.  Past the end of the row the row's last float4 is
 // loaded again (V is a multiple of 4): every load is unconditional, so the compiler can
-// wait for the older loads only, and the callers skip those entries (or, for the row
-// maximum, take them: they repeat real elements).
+// wait for the older loads only, and the callers skip those entries.
 constexpr int VR = 2;  // float4 a thread per step of the row passes (the segment pass: VU)
 constexpr int VU = 2;
 AS_DEVICE void load_step(const float *z, int V, int i0, float4 (&v)[VR]) {
@@ -925,26 +925,9 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
   const float *z = a.logits + (size_t)row * V;
   const int nseg = (V + SEG - 1) / SEG;
 
-  // ---- pass 0: row max (+inf when a logit is not finite) -------------------------------
-  float mx = -INFINITY;
   if (tid == 0) sm.flag = 0;
-  if (SPLIT) {
-    mx = split_view(a, row).st->sel.M;
-  } else if (a.tile_max) {  // the LM head's epilogue left the row's maximum per column tile
-    const float *tm = a.tile_max + (size_t)row * a.ntile;
-    for (int t = tid; t < a.ntile; t += VT) mx = max_or_inf(mx, tm[t]);
-  } else {
-    for (RowStream rs(z, V, tid * 4); rs.more(); rs.advance()) {
-      rs.prefetch();
-      const float4 (&vv)[VR] = rs.cur;
-#pragma unroll
-      for (int u = 0; u < VR; ++u)
-        mx = max_or_inf(max_or_inf(max_or_inf(max_or_inf(mx, vv[u].x), vv[u].y), vv[u].z),
-                        vv[u].w);
-    }
-  }
   Sel sel;
-  sel.M = block_max(mx, sm);
+  sel.M = SPLIT ? split_view(a, row).st->sel.M : tile_row_max(a, row, sm);
   sel.c_hi = a.c_hi;
   sel.c_lo = a.c_lo;
   const bool tail = a.tail != 0;
@@ -1335,10 +1318,10 @@ namespace acespec {
 // ids 249 / 312), 384 with top_p 1, whose threshold lies among few ids, so that whole rows
 // need one pass less (384 rows 97 / 92 and 172 / 173, 448 rows 111 / 93 and 204 / 178).
 // Beyond 512 rows there are not two chunks a row for the workgroups that the CUs hold.
-int vocab_chunks(int rows, int V, float top_p, bool have_max) {
+int vocab_chunks(int rows, int V, float top_p) {
   const int most = V < 20000 ? 0 : V < 24000 ? 32 : V < 48000 ? 128
                                      : top_p < 1.f ? kVocabSplitRows : 384;
-  if (!have_max || rows < 1 || rows > most) return 1;
+  if (rows < 1 || rows > most) return 1;
   const int nseg = (V + SEG - 1) / SEG;
   int c = 1024 / rows;   // every CU holds four of the chunks' workgroups
   if (c > 32) c = 32;
@@ -1346,14 +1329,15 @@ int vocab_chunks(int rows, int V, float top_p, bool have_max) {
   return c < 1 ? 1 : c;
 }
 size_t vocab_split_bytes(int rows, int V) {
-  const int c = vocab_chunks(rows, V, 0.f, true);   // (the most that any top_p takes)
+  const int c = vocab_chunks(rows, V, 0.f);   // (the most that any top_p takes)
   return c > 1 ? (size_t)rows * split_row_bytes(c, (V + SEG - 1) / SEG) : 0;
 }
 
 hipError_t launch_vocab(const VocabArgs &args, hipStream_t s) {
-  if (args.V > SEGMAX * SEG || args.k > KMAX || args.k < 1) return hipErrorInvalidValue;
+  if (args.V > SEGMAX * SEG || args.k > KMAX || args.k < 1 || !args.tile_max)
+    return hipErrorInvalidValue;
   VocabArgs a = args;
-  a.chunks = vocab_chunks(a.rows, a.V, a.top_p, a.tile_max != nullptr);
+  a.chunks = vocab_chunks(a.rows, a.V, a.top_p);
   const dim3 rows(a.rows), parts(a.rows * a.chunks), block(VT);
   if (a.chunks == 1 || !a.split || vocab_split_bytes(a.rows, a.V) > a.split_bytes) {
     hipLaunchKernelGGL(vocab_verify_kernel<false>, rows, block, 0, s, a);
