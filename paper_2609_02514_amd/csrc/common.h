@@ -335,8 +335,8 @@ struct VocabArgs {
   float *topk_probs;
 };
 hipError_t launch_vocab(const VocabArgs &a, hipStream_t s);
-// Rows up to which a row's passes are split over several workgroups, and the scratch that
-// takes (0: not split).
+// Rows up to which a row's passes are split over several workgroups (fewer for short rows and
+// with top_p 1), and the scratch that takes (0: not split).
 constexpr int kVocabSplitRows = 512;
 size_t vocab_split_bytes(int rows, int V);
 

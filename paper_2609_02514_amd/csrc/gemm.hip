@@ -1094,7 +1094,7 @@ int pick_variant(int epi, int M, int N, int K, int packed) {
     // one (40 instead of 48 KB a CU per k-step at 128 rows), so from ~500 rows the
     // products take 128 x 512 tiles (64 x 512 for the residual product with a short K
     // at ~520 rows, where 128-row tiles leave most of a last round empty); fewer rows take
-    // 128 x 128 ones (and up to 288 rows most products run in gemm_rows_kernel).
+    // 128 x 128 ones (where rows_ok does not give them to gemm_rows_kernel).
     if (M <= 384) return 5;
     return K < 8192 && M <= 640 ? 8 : 7;
   }
@@ -1133,7 +1133,9 @@ RowsPlan plan_rows(int epi, int M, int N, int K, int cus, long long cap, int es 
 // Where it runs.  Against the 128 x 128, 288 x 64 and 128 x 256 tiles it takes the place of
 // (8B / 1B shapes, us): gate/up at 138 rows 47 for 87 (packed) and 52 for 142 (row-major),
 // at 272 rows 25 for 31 (1B); beyond 288 rows the larger tiles are faster (packed, 384 rows:
-// 98 against 114).  The residual products keep it longer (down at 520 rows: 77 for 97
+// 98 against 114).  Up to there it is 1.6 times as fast as the tiles before it on average (gate/up
+// 1024 x 2048 .. 8192 x 28672, residual 1024 x 1024 .. 8192 x 28672), and where one of today's
+// tiles is faster, by 20 % (gate/up) and 13 % at most.  The residual products keep it longer (down at 520 rows: 77 for 97
 // row-major), up to widths whose weights need several rounds of its tiles a k-slice: packed
 // 32 Mi elements (8B-class, 432 rows: 79 against 71), row-major 64 Mi (us, against 128 x 256
 // and 256 x 256 tiles: 8192 x 8192, 512 rows 105 against 114; 5120 x 27648, 448 rows 242
