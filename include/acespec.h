@@ -216,7 +216,8 @@ int acespec_verify_tail(acespec_ctx *ctx, const void *lm_head, acespec_layout lm
  * R is limited by the array: R * (4 + 4 ceil(vocab / 128) + d_model * 2) bytes (d_model * 4
  * for an fp32 model with a final norm; no d_model term for an fp32 model without one) must
  * fit in 48 MiB, else ACESPEC_EINVAL before anything is launched (e.g. R <= 4096 at
- * d_model 4096, vocab 128256).  The LM head is never sliced along K here.
+ * d_model 4096, vocab 128256).  The LM head is never sliced along K here (where
+ * acespec_verify_tail slices it, the logits differ in the order of their fp32 sums).
  * All calls on one device share the array: two calls that overlap in time on the same
  * device race (serialise them, e.g. on one stream).  Every byte a call reads from the
  * array it has written first, so no clearing is needed between calls. */

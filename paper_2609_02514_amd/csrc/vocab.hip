@@ -546,12 +546,14 @@ AS_DEVICE u64 nucleus_target(float top_p, u64 S) {
   return T > S ? S : T;
 }
 
-// Whether row r has drafted children (the tail: every row has one).
+// Whether row r has drafted children (the tail: every row has one).  Every lane of the wave
+// calls it and looks at a row of its own: one row after the other, each a load of its own,
+// took 9 us of a 65-row tree's 45 (65 rows of 4096 ids).
 AS_DEVICE bool row_has_child(const acespec::VocabArgs &a, size_t srow0, int r) {
   if (a.tail) return true;
   bool any = false;
-  for (int c = r + 1; c < a.n1; ++c) any |= a.par[srow0 + c] == r;
-  return any;
+  for (int c = r + 1 + (threadIdx.x & 63); c < a.n1; c += 64) any |= a.par[srow0 + c] == r;
+  return __any(any);
 }
 
 // The row's maximum from the LM head's column tiles (+inf when a logit is not finite).
@@ -959,6 +961,8 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
     return;
   }
 
+  const bool has_child = row_has_child(a, srow0, r);
+
   // (a list that does not hold exactly the top-k ids is not used: its other slots are an
   // earlier call's)
   const RowState *st0 = SPLIT ? split_view(a, row).st : nullptr;
@@ -1165,14 +1169,13 @@ __global__ __launch_bounds__(VT, 6) void vocab_verify_kernel(acespec::VocabArgs 
   }
 
   // ---- pass 4: id-ordered segments: masses of p_r and of the residual, top-k ids ----------
-  const bool resid = !a.q_scalar && row_has_child(a, srow0, r);
+  const bool resid = !a.q_scalar && has_child;
   const bool badq = segment_pass(
       z, resid ? a.q + (size_t)row * V : nullptr, V, 0, nseg, resid, sel, sm,
       [&](int sg, uint32_t &tp, uint32_t &tk) { tp = sm.g.tie_p[sg]; tk = sm.g.tie_k[sg]; },
       sm.g.seg_p, sm.g.seg_r);
   if (__syncthreads_or(badq) && tid == 0) sm.flag = ACESPEC_EBADDRAFT;
   }
-  const bool has_child = row_has_child(a, srow0, r);
   // Scalar mode: the uplink carries only q-hat of each drafted token (one float per
   // child row); the cloud then tests acceptance and does no sampling, so the residual
   // mass (the only reader of a dense q row) is not needed.
